@@ -218,7 +218,8 @@ def prepare(case, seed):
     st = dict(family=fam, sv=sv, steps=case["steps"])
     if fam == "analysis":
         return st
-    st["start"] = sv.U.clone()
+    top = 1 + int(sv.blocks()[:, 0].max())   # the slots in use: the capacity is that of the full tree
+    st["start"] = sv.U[:top].clone()
     if fam in ("uniform", "lts"):
         return st
     # a start from which the tree stays as it is over a pass
@@ -228,7 +229,8 @@ def prepare(case, seed):
         after = sv.blocks()
         if before.shape == after.shape and (before == after).all():
             break
-        st["start"].copy_(sv.U)
+        top = 1 + int(after[:, 0].max())
+        st["start"] = sv.U[:top].clone()
     return st
 
 
@@ -244,13 +246,14 @@ def run(state):
         flags, det = sv.mr_flag()
         X, slots = mrfv.solver_features(sv)
         return {"U": sv.U, "flags": flags, "details": det, "dt": sv.cfl_dt(), "totals": sv.totals(), "features": X}
-    sv.U.copy_(state["start"])
+    U = sv.U[:state["start"].shape[0]]
+    U.copy_(state["start"])
     if state["family"] == "lts":
         sv.step_lts()
     else:
         sv.run(state["steps"])
     sv.mr_project()
-    return _interior(sv.U)
+    return _interior(U)
 
 
 # Share of the full tree's leaves that the jump trees hold (about, by levels), for work().
