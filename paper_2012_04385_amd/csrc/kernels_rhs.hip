@@ -796,7 +796,9 @@ struct LdsSink {
     __device__ void face(int side, int q, T v) { FF[(side * 5 + q) * FACE + rm] = v; }
 };
 
-// One workgroup per leaf.  The block is walked in groups of GP z-planes; for each group
+// One workgroup per leaf, or per slab of a leaf's planes where the leaves alone leave CUs idle
+// (slab_split: 8 leaves, ten steps, 3130 -> 988 us; 592 leaves with the HLLC kernel 3150 -> 2818
+// us a pass of two steps).  The block is walked in groups of GP z-planes; for each group
 // every x-, y- and z-face flux the group's cells need is computed once, one face per
 // thread (coalesced, L1-resident six-cell stencils; all axes share one code path), and
 // staged in LDS.  Each thread then owns one (x, y) column: it forms
@@ -810,6 +812,30 @@ struct LdsSink {
 // D in the same order, so all give bitwise the same result.
 constexpr int NFZ = NI * NI;                  // z-faces per face plane (256)
 
+// Slabs a leaf's planes are split into over workgroups (a power of two, at most 8 and at most
+// the kernel's groups).  A workgroup alone on its CU takes 93 us for a whole leaf, two at
+// once 146 us together (the chip holds two per CU), so a launch lasts about as long as its
+// fullest CU: 73 units per pair member, 93 for an odd one out, times the slab's share of the
+// leaf's faces.  Each slab repeats one plane of 256 z-faces beside 1600 per group of two
+// planes and starts and drains its own pipeline (taken as 500 faces).  The split with the
+// least of that is taken, the smaller on ties: 8 leaves go to 64 workgroups, 592
+// leaves (three on the fullest CU) to 1184, 512 leaves (two on every CU) and large trees
+// stay whole.  Split launches have at most SLAB_ITEMS workgroups, so a graph's grid is bounded.
+constexpr int SLAB_ITEMS = 4096;
+__host__ __device__ inline int slab_split(int nleaf, int most) {
+    if (nleaf > SLAB_ITEMS / 2) return 1;
+    int best = 0, best_t = 0;
+    for (int b = 0; b < 4; ++b) {   // 2^b slabs
+        if ((1 << b) > most || (nleaf << b) > SLAB_ITEMS) break;
+        const int load = ((nleaf << b) + 255) >> 8;
+        const int t = (73 * (load & ~1) + 93 * (load & 1)) * ((8 * 1600 >> b) + 256 + 500);
+        if (b == 0 || t < best_t) {
+            best = b;
+            best_t = t;
+        }
+    }
+    return 1 << best;
+}
 
 // Sources of one workgroup's stencils as 32-bit byte offsets from the lowest of them,
 // read through one buffer resource (range-checked: out-of-range reads return zero);
@@ -827,12 +853,12 @@ __device__ __forceinline__ float buffer_f32(__amdgpu_buffer_rsrc_t r, unsigned v
 
 // Face flux along axis D for the stencil starting at padded index base (six cells at
 // base + j*stride, padded coordinate pos0 + j along D); cells below / above the interior
-// come from lo / hi, which are the neighbour's block shifted by -+16 cells along D (or
-// the own block).  The result is returned in physical component order.
-template <typename T, int D, int SCH>
-__device__ __forceinline__ void face_flux_at(const T *__restrict__ ub, const T *__restrict__ lo,
-                                             const T *__restrict__ hi, const NearSrc &ns, int base,
-                                             int pos0, const Gas<T> &G, T Fp[5]) {
+// come from source(side), the neighbour's block shifted by -+16 cells along D (or the
+// own block).  The result is returned in physical component order.
+template <typename T, int D, int SCH, class Source>
+__device__ __forceinline__ void face_flux_at(const T *__restrict__ ub, const Source &source,
+                                             const NearSrc &ns, int base, int pos0,
+                                             const Gas<T> &G, T Fp[5]) {
     constexpr int stride = Axes<D>::STRIDE;
     constexpr int n1 = Axes<D>::N1, t1 = Axes<D>::T1, t2 = Axes<D>::T2;   // rotated components
     CellState<T> w[6];
@@ -862,6 +888,7 @@ __device__ __forceinline__ void face_flux_at(const T *__restrict__ ub, const T *
             }
         }
     } else {
+        const T *lo = source(2 * D), *hi = source(2 * D + 1);
 #pragma unroll
         for (int j = 0; j < 6; ++j) {
             const int pos = pos0 + j;
@@ -881,8 +908,14 @@ __device__ __forceinline__ void face_flux_at(const T *__restrict__ ub, const T *
     Fp[t2] = F[3];
 }
 
+// Wavefronts per SIMD the registers are allocated for when the launch shape asks for none:
+// two 512-thread workgroups per CU (which their LDS admits) need four, i.e. at most 128
+// registers; the Roe-TENO5 kernel came out at 131 without this and ran one per CU.
+constexpr int rhs_waves(int wpe, int gp, int tpb) { return wpe == 1 && gp <= 2 && tpb == 512 ? 4 : wpe; }
+
 template <typename T, int GP, int TPB_F, bool PERSIST, int WPE, int SCH>
-__global__ __attribute__((amdgpu_flat_work_group_size(TPB_F, TPB_F), amdgpu_waves_per_eu(WPE)))
+__global__ __attribute__((amdgpu_flat_work_group_size(TPB_F, TPB_F),
+                          amdgpu_waves_per_eu(PERSIST ? WPE : rhs_waves(WPE, GP, TPB_F))))
 void k_rhs_update(int stage, const double *__restrict__ dt,
                                                       const T *__restrict__ Uin, T *__restrict__ Uout,
                                                       T *U0, WorkList wl,
@@ -908,37 +941,41 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
     __shared__ T Fz[NZR][NI][NI][5];         // [face plane mod NZR][y][x][q]
     __shared__ int next_chunk[2];            // per buffer: first face not yet handed out
     __shared__ double cfl_acc[3][FACE];      // with cflmax: per owner column, the speed maxima
-    // one workgroup per leaf in XCD-aware order (graph launches size the grid by the slot
-    // capacity and surplus groups exit), or, persistent, a fixed grid looping over the leaves
+    // one workgroup per leaf, or per slab of a leaf's planes on small trees, in XCD-aware order
+    // (graph launches size the grid by the slot capacity and surplus groups exit), or,
+    // persistent, a fixed grid looping over them.  The last stage's CFL maxima have
+    // CFL_SLABS places per leaf.
     const int nleaf = wl.count();
-    auto block = [&](int b) __attribute__((always_inline)) {
-    const int slot = wl.at(b);
+    constexpr int NGRP = NI / GP, MAX_SLABS = NGRP < 8 ? NGRP : 8;
+    const int nsl = slab_split(nleaf, cflmax ? min(MAX_SLABS, CFL_SLABS) : MAX_SLABS);
+    auto block = [&](int item) __attribute__((always_inline)) {
+    const int slab = item & (nsl - 1);
+    const int g_lo = slab * (NGRP / nsl), g_hi = g_lo + NGRP / nsl;   // this workgroup's groups
+    const int slot = wl.at(item / nsl);
     const BlockMeta mt = meta[slot];
-    const InstDev P = inst[mt.inst];
+    const InstDev P = inst[mt.inst];   // a copy: reading it in the update cost 1.3 % on 512 leaves
     const Gas<T> G = gas_of<T>(P);
     const T *ub = Uin + (size_t)slot * 5 * CELLS_P;
     T *ob = Uout + (size_t)slot * 5 * CELLS_P;
-    // per face side: the same-level neighbour shifted so that own padded indices address
-    // its interior, or the own block (halo filled) at jumps and zero-gradient boundaries
-    const T *nlo[3], *nhi[3];
-    {
-        const int freg[6] = {12, 14, 10, 16, 4, 22};
-        const int strd[3] = {1, NP, NP * NP};
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const int sl = (mt.zg >> (2 * a)) & 1 ? -1 : nbr[(size_t)slot * 27 + freg[2 * a]];
-            const int sh = (mt.zg >> (2 * a + 1)) & 1 ? -1 : nbr[(size_t)slot * 27 + freg[2 * a + 1]];
-            nlo[a] = sl >= 0 ? Uin + (size_t)sl * 5 * CELLS_P + NI * strd[a] : ub;
-            nhi[a] = sh >= 0 ? Uin + (size_t)sh * 5 * CELLS_P - NI * strd[a] : ub;
-        }
-    }
+    // source of the cells beyond a face: the same-level neighbour shifted so that own padded
+    // indices address its interior, or the own block (halo filled) at jumps and boundaries.
+    // Read again where a far workgroup needs it: twelve scalar registers less in the loop.
+    auto source = [&](int side) __attribute__((always_inline)) {
+        const int a = side >> 1;
+        const int n = (mt.zg >> side) & 1 ? -1 : nbr[(size_t)slot * 27 + face_region(side)];
+        const int shift = NI * (a == 0 ? 1 : (a == 1 ? NP : NP * NP));
+        return n >= 0 ? Uin + (size_t)n * 5 * CELLS_P + (side & 1 ? -shift : shift) : ub;
+    };
     NearSrc ns;
     {
+        uintptr_t nlo[3], nhi[3];
         uintptr_t mn = (uintptr_t)ub, mx = (uintptr_t)ub;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            mn = min(mn, min((uintptr_t)nlo[a], (uintptr_t)nhi[a]));
-            mx = max(mx, max((uintptr_t)nlo[a], (uintptr_t)nhi[a]));
+            nlo[a] = (uintptr_t)source(2 * a);
+            nhi[a] = (uintptr_t)source(2 * a + 1);
+            mn = min(mn, min(nlo[a], nhi[a]));
+            mx = max(mx, max(nlo[a], nhi[a]));
         }
         // every access lies below the highest source plus one block
         const uintptr_t span = mx - mn + (uintptr_t)(5 * CELLS_P * sizeof(T));
@@ -951,8 +988,8 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
         ns.own = (unsigned)((uintptr_t)ub - mn);
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            ns.lo[a] = (unsigned)((uintptr_t)nlo[a] - mn);
-            ns.hi[a] = (unsigned)((uintptr_t)nhi[a] - mn);
+            ns.lo[a] = (unsigned)(nlo[a] - mn);
+            ns.hi[a] = (unsigned)(nhi[a] - mn);
         }
     }
     T *ffs = FF + (size_t)slot * 6 * 5 * FACE;
@@ -1051,10 +1088,10 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
     };
 
     // faces of group g: x-faces (plane p, row y, face f), y-faces (plane p, face f,
-    // column x), then the z-face planes the group adds (all GP + 1 for the first group)
+    // column x), then the z-face planes the group adds (all GP + 1 for the slab's first group)
     auto group_faces = [&](int g) {
         const int k0 = g * GP;
-        const int first_z = g == 0 ? 0 : 1;
+        const int first_z = g == g_lo ? 0 : 1;
         const int total = 2 * NFX + (GP + 1 - first_z) * NFZ;
         const int buf = g & 1;
         const int lane = tid & 63;
@@ -1079,7 +1116,7 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
                     p = v / (NF_OUT * NI);
                 }
                 const int base = ((k0 + p + HW) * NP + y + HW) * NP + f + 1;
-                face_flux_at<T, 0, SCH>(ub, nlo[0], nhi[0], ns, base, f + 1, G, F);
+                face_flux_at<T, 0, SCH>(ub, source, ns, base, f + 1, G, F);
 #pragma unroll
                 for (int q = 0; q < 5; ++q) Fx[buf][p][y][f][q] = F[q];
                 if (f == 0 || f == NI) {
@@ -1100,7 +1137,7 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
                     p = v / (NI * NF_OUT);
                 }
                 const int base = ((k0 + p + HW) * NP + f + 1) * NP + x + HW;
-                face_flux_at<T, 1, SCH>(ub, nlo[1], nhi[1], ns, base, f + 1, G, F);
+                face_flux_at<T, 1, SCH>(ub, source, ns, base, f + 1, G, F);
 #pragma unroll
                 for (int q = 0; q < 5; ++q) Fy[buf][p][f][x][q] = F[q];
                 if (f == 0 || f == NI) {
@@ -1112,7 +1149,7 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
                 const int x = u % NI, y = (u / NI) % NI, j = u / NFZ + first_z;
                 const int kf = k0 + j;          // face between interior planes kf-1 and kf
                 const int base = ((kf + 1) * NP + y + HW) * NP + x + HW;   // padded z = kf+1 .. kf+6
-                face_flux_at<T, 2, SCH>(ub, nlo[2], nhi[2], ns, base, kf + 1, G, F);
+                face_flux_at<T, 2, SCH>(ub, source, ns, base, kf + 1, G, F);
 #pragma unroll
                 for (int q = 0; q < 5; ++q) Fz[kf % NZR][y][x][q] = F[q];
                 if (kf == 0 || kf == NI) {
@@ -1142,20 +1179,21 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
 #pragma unroll
         for (int d = 0; d < 3; ++d) cfl_acc[d][tid] = 0.0;
     __syncthreads();
-    // iteration g: update group g (g >= 0) and compute the faces of group g + 1
+    // iteration g: update group g (g >= g_lo) and compute the faces of group g + 1
 #pragma unroll 1
-    for (int g = -1; g < NI / GP; ++g) {
-        if (g >= 0 && owner) group_update(g);
-        if (g + 1 < NI / GP) group_faces(g + 1);
+    for (int g = g_lo - 1; g < g_hi; ++g) {
+        if (g >= g_lo && owner) group_update(g);
+        if (g + 1 < g_hi) group_faces(g + 1);
         // group g's counter is free again (its faces were done before the last barrier);
         // group g + 2 takes it after the next one
-        if (g >= 0 && tid == 0) next_chunk[g & 1] = 0;
+        if (g >= g_lo && tid == 0) next_chunk[g & 1] = 0;
         __syncthreads();
     }
     if (!ok) atomicOr(err, 1);
     if (cflmax) {
-        // block maxima of the signal speeds (the CFL pass's values, stored as the first slab's
-        // maxima, the other slabs zero): over each owner wavefront, then over the four
+        // maxima of the signal speeds (the CFL pass's values, stored as the maxima of the first
+        // of the CFL slabs this workgroup covers, the others zero): over each owner
+        // wavefront, then over the four
         double m[3];
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
@@ -1171,20 +1209,19 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
             double v = cfl_acc[tid][0];
 #pragma unroll
             for (int w = 1; w < FACE / 64; ++w) v = fmax(v, cfl_acc[tid][w]);
-            double *bm = cflmax + (size_t)mt.lpos * CFL_SLABS * 3;   // by all-leaves position
+            double *bm = cflmax + ((size_t)mt.lpos * CFL_SLABS + slab * (CFL_SLABS / nsl)) * 3;   // by all-leaves position
             bm[tid] = v;
-#pragma unroll
-            for (int k = 1; k < CFL_SLABS; ++k) bm[k * 3 + tid] = 0.0;
+            for (int k = 1; k < CFL_SLABS / nsl; ++k) bm[k * 3 + tid] = 0.0;
         }
         __syncthreads();   // cfl_acc is cleared again for a persistent grid's next block
     }
     };
     if constexpr (PERSIST) {
-        for (int b = blockIdx.x; b < nleaf; b += gridDim.x) block(b);   // uniform per workgroup
+        for (int b = blockIdx.x; b < nleaf * nsl; b += gridDim.x) block(b);   // uniform per workgroup
     } else {
-        // the grid covers every leaf; the loop-free form keeps the register count down
-        const int b = xcd_item(blockIdx.x, gridDim.x, nleaf);
-        if (b < nleaf) block(b);
+        // the grid covers every slab; the loop-free form keeps the register count down
+        const int b = xcd_item(blockIdx.x, gridDim.x, nleaf * nsl);
+        if (b < nleaf * nsl) block(b);
     }
 }
 
@@ -1306,7 +1343,11 @@ static void launch_variant(int stage, const double *dt, const float *Uin, float 
     constexpr int G = RHS_GP[V], B = RHS_TPB[V];
     constexpr bool PS = RHS_PERSIST[V];
     constexpr int WP = RHS_WPE[V];
-    const int grid = PS ? std::min(wl.grid, persist_grid(B)) : round_xcd(wl.grid);
+    // every slab of every leaf: exactly (eager), or for any number of leaves up to the bound
+    int items = wl.desc ? wl.grid : wl.n * slab_split(wl.n, 8);
+    if (wl.desc)
+        for (int n = 1; n <= std::min(wl.grid, SLAB_ITEMS); ++n) items = std::max(items, n * slab_split(n, 8));
+    const int grid = PS ? std::min(items, persist_grid(B)) : round_xcd(items);
     hipLaunchKernelGGL((k_rhs_update<float, G, B, PS, WP, SCH>), dim3(grid), dim3(B), 0, st, stage, dt, Uin,
                        Uout, U0, wl, tb.meta, tb.nbr, inst, FF, err, restrict_parents, cflmax,
                        RHS_PTR[V] ? 1 : 0);
