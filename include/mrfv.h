@@ -56,9 +56,9 @@ typedef enum { MRFV_ROE_WENO5 = 0, MRFV_ROE_TENO5 = 1, MRFV_LLF_WENO5 = 2,
  * a dependent variable, is not evolved and stays zero (the initial pressure is unused).
  * The flux is the standard configuration's characteristic WENO5-JS Roe solver with
  * per-field LLF fallback on the four fields (u-c, u, u, u+c), Roe c~^2 = (p_R - p_L) /
- * (rho_R - rho_L).  Tait runs on the plain kernels: contexts with it must use scheme
- * MRFV_ROE_WENO5, no gravity, no proposer, and not the fused FP32 path (batched with
- * MRFV_F32); mrfv_create returns MRFV_EINVAL otherwise. */
+ * (rho_R - rho_L).  Contexts with it must use scheme
+ * MRFV_ROE_WENO5, no gravity, no proposer, and not batched with MRFV_F32; mrfv_create
+ * returns MRFV_EINVAL otherwise. */
 typedef enum { MRFV_STIFFENED_GAS = 0, MRFV_TAIT = 1 } mrfv_eos;
 /* External boundaries per axis: periodic; zero gradient (every halo layer a copy of the
  * boundary cell); symmetry (the halo is the mirror image of the interior with the
@@ -97,11 +97,11 @@ typedef struct {
                              (normal: the two cells sharing the face; tangential: the mean
                              of their central differences).  dt is then also bounded by
                              cfl * 3/16 * dx_lmax^2 * min(rho) / mu.  Viscous contexts
-                             (any instance with mu > 0) run on the plain kernels and fill
-                             all 26 halo regions of the leaves every stage (the
-                             tangential derivatives read the edge halos); mrfv_create
-                             returns MRFV_EINVAL for one on the fused FP32 path (batched
-                             with MRFV_F32), mrfv_step_lts returns MRFV_EINVAL for one. */
+                             (any instance with mu > 0) evaluate the right-hand side and
+                             update in separate kernels and fill all 26 halo regions of the
+                             leaves every stage (the tangential derivatives read the edge
+                             halos); mrfv_create returns MRFV_EINVAL for one with batched
+                             and MRFV_F32, mrfv_step_lts returns MRFV_EINVAL for one. */
     const double *bc_fixed;   /* host, read by mrfv_create only; required when some axis
                              has MRFV_BC_FIXED, else ignored (may be NULL): primitive states
                              (rho, u, v, w, p) of the halo cells beyond the sides of those
@@ -114,10 +114,14 @@ typedef struct {
     int32_t dtype;          /* mrfv_dtype of U, U0, L                                   */
     int32_t n_instances;    /* >= 1                                                     */
     int32_t slot_capacity;  /* maximum number of blocks over all instances              */
-    int32_t batched;        /* 0: plain path (one launch per tree level, unfused update);
-                               1: batched path (all leaves of all levels and instances in
-                               one fused rhs + update launch; fused for FP32 only);
-                               2: batched path with the CFL step and the three RK stages
+    int32_t batched;        /* every context integrates all leaves of all levels and
+                               instances in one fused rhs + update launch per stage (two
+                               more state buffers of mrfv_state_bytes; viscous contexts, and
+                               ones for which that memory is not there, take an rhs and an
+                               update launch);
+                               1: with MRFV_F32 also the entry points that need the two
+                               buffers at creation (mrfv_fused_stage, mrfv_autotune);
+                               2: as 1, with the CFL step and the three RK stages
                                replayed from one hipGraph (captured on first use, valid
                                across tree changes; FP32)                              */
     int32_t scheme;         /* mrfv_scheme: the flux kernel of every leaf               */
@@ -268,8 +272,7 @@ int mrfv_run(mrfv_ctx *ctx, void *U, void *U0, void *L, double *dt_dev, int32_t 
  * replaces its own sum by the fine average at the end of its step (coarse cell
  * adjustment).  Adaptive instances run mr_flag, commit_flags and mr_predict once, after
  * the last micro step.  Runs per tree level in the context's dtype (any batched mode):
- * in FP32 the fused stage kernel evaluates the flux divergence (Tait's system: the plain
- * flux kernel), in FP64 the plain flux kernel; separate kernels integrate it.  U0: dev
+ * the fused stage kernel evaluates the flux divergence; separate kernels integrate it.  U0: dev
  * scratch of mrfv_interior_bytes, as for mrfv_step; L is not used
  * (may be NULL); the library allocates its padded flux-divergence field, the jump-halo
  * stage state and the face-flux sums on first use (MRFV_ENOMEM if it cannot).  cell_updates_host (may be
@@ -298,8 +301,8 @@ int mrfv_refine_block(mrfv_ctx *ctx, void *U, int32_t instance, int32_t level, i
 int mrfv_coarsen_block(mrfv_ctx *ctx, int32_t instance, int32_t level, int32_t bx,
                        int32_t by, int32_t bz);
 
-/* Kernel timing: when enabled, every launch of the fused rhs + update kernel (batched
- * path) or of the flux kernel (plain path) is bracketed by HIP events on the context
+/* Kernel timing: when enabled, every launch of the fused rhs + update kernel (or of its
+ * right-hand side alone) is bracketed by HIP events on the context
  * stream; mrfv_kernel_time returns the number of timed launches, their total duration in
  * ms and the leaf cells per launch summed over launches. */
 int mrfv_enable_kernel_timing(mrfv_ctx *ctx, int32_t on);

@@ -166,7 +166,7 @@ int do_project(mrfv_ctx *ctx, T *U, bool stage_only = false, bool rho_e_only = f
 // Halo fill, levels coarse to fine (a prediction reads the parent's filled halo).
 // Non-leaf blocks always get all 26 regions (they are prediction sources); leaves get
 //   FILL_ALL: all 26 regions (explicit fill, refinement);
-//   FILL_FACES: the face layers the flux reads (plain stages);
+//   FILL_FACES: the face layers the flux reads (stages through L);
 //   FILL_MISSING_FACES: faces without a same-level neighbour (fused stages, which read
 //   same-level neighbours in place);
 //   FILL_MISSING: all regions without a same-level neighbour (before the details, which
@@ -232,41 +232,6 @@ void timing_end(mrfv_ctx *ctx, hipEvent_t a, int64_t cells) {
     ctx->ev_cells.push_back(cells);
 }
 
-// Flux differences D and boundary fluxes for all leaves, with the jump correction.
-template <typename T>
-int do_flux(mrfv_ctx *ctx, const T *U) {
-    const HostLists &L = ctx->lists;
-    if (!ctx->d_D) {   // the fused batched path never needs it; allocate on first use
-        HIP_OK(hipStreamSynchronize(ctx->stream));
-        if (hipMalloc(&ctx->d_D, (size_t)ctx->cfg.slot_capacity * 3 * 5 * CELLS_I * sizeof(T)) !=
-            hipSuccess) {
-            ctx->d_D = nullptr;
-            return fail(ctx, MRFV_ENOMEM, "hipMalloc of the flux-difference scratch failed");
-        }
-    }
-    T *D = (T *)ctx->d_D, *FF = (T *)ctx->d_FF;
-    hipEvent_t ev{};
-    timing_begin(ctx, &ev);
-    if (ctx->cfg.batched) {
-        HIP_OK(launch_flux<T>(flux_kernel(ctx), U, wlist(ctx, DESC_LEAVES), ctx->tb, ctx->d_inst, D, FF, ctx->stream));
-    } else {
-        for (int l = 0; l <= L.max_level; ++l)
-            HIP_OK(launch_flux<T>(flux_kernel(ctx), U, wlist(ctx, desc_leaf(l)), ctx->tb, ctx->d_inst, D, FF,
-                                  ctx->stream));
-    }
-    timing_end(ctx, ev, (int64_t)L.all_leaves_cnt * CELLS_I);
-    // viscous terms: subtracted from the differences and face planes before the jump
-    // correction averages the (total) fine fluxes
-    if (ctx->viscous)
-        HIP_OK(launch_visc<T>(U, wlist(ctx, DESC_LEAVES), ctx->tb, ctx->d_inst, D, FF, ctx->stream));
-    if (ctx->has_jumps) {
-        for (int l = L.max_level - 1; l >= 0; --l)
-            HIP_OK(launch_ff_restrict<T>(FF, wlist(ctx, desc_par(l)), ctx->tb, ctx->stream));
-        HIP_OK(launch_reflux<T>(D, FF, wlist(ctx, DESC_LEAVES), ctx->tb, ctx->stream));
-    }
-    return MRFV_OK;
-}
-
 // CFL time step of eq:Cfl per instance and, for viscous instances, the viscous bound.
 template <typename T>
 int do_cfl(mrfv_ctx *ctx, const T *U, double *dt) {
@@ -279,13 +244,28 @@ int do_cfl(mrfv_ctx *ctx, const T *U, double *dt) {
     return MRFV_OK;
 }
 
+// Flux divergence L of all leaves, with the viscous terms and the jump correction.
+// own_halo: every halo is filled and the stencils read it; else same-level neighbours are read
+// in place.
 template <typename T>
-int do_rhs(mrfv_ctx *ctx, const T *U, T *Lout) {
-    CALL(do_flux<T>(ctx, U));
+int do_rhs(mrfv_ctx *ctx, const T *U, T *Lout, bool own_halo) {
     const HostLists &L = ctx->lists;
-    (void)L;
-    HIP_OK(launch_combine<T>((const T *)ctx->d_D, Lout, wlist(ctx, DESC_LEAVES), ctx->tb,
-                             ctx->d_inst, U, ctx->stream));
+    T *FF = (T *)ctx->d_FF;
+    hipEvent_t ev{};
+    timing_begin(ctx, &ev);
+    HIP_OK(launch_rhs_update<T>(flux_kernel(ctx), ctx->rhs_variant, RHS_TO_L, nullptr, U, Lout, nullptr,
+                                wlist(ctx, DESC_LEAVES, 1 << 30), ctx->tb, ctx->d_inst, FF, ctx->d_err, 0,
+                                nullptr, own_halo, ctx->stream));
+    timing_end(ctx, ev, (int64_t)L.all_leaves_cnt * CELLS_I);
+    // viscous terms: added to L and taken from the face planes before the jump correction
+    // averages the (total) fine fluxes
+    if (ctx->viscous)
+        HIP_OK(launch_visc<T>(U, wlist(ctx, DESC_LEAVES), ctx->tb, ctx->d_inst, Lout, FF, ctx->stream));
+    if (ctx->has_jumps) {
+        for (int l = L.max_level - 1; l >= 0; --l)
+            HIP_OK(launch_ff_restrict<T>(FF, wlist(ctx, desc_par(l)), ctx->tb, ctx->stream));
+        HIP_OK(launch_reflux<T>(Lout, FF, wlist(ctx, DESC_JCORR), ctx->tb, ctx->d_inst, ctx->stream));
+    }
     return MRFV_OK;
 }
 
@@ -296,22 +276,43 @@ int do_update(mrfv_ctx *ctx, int stage, const double *dt, T *U, T *U0, const T *
     return MRFV_OK;
 }
 
-// One stage of the batched path: fused rhs + update over all leaves, then the jump
-// correction on the updated state.
-int do_stage_fused(mrfv_ctx *ctx, int stage, const double *dt, const float *Uin, float *Uout,
-                   float *U0, bool restrict_parents = false, double *cflmax = nullptr) {
+// Whether the stages run fused, out of place through the state buffers W and W2 (every
+// context but the viscous ones, and those whose buffers could not be had).
+bool fused_stages(const mrfv_ctx *ctx) { return ctx->d_W && ctx->d_W2 && !ctx->viscous; }
+
+// Contexts that did not get W and W2 when they were created (all but batched FP32) allocate
+// them with their first tree (steps allocate nothing, so that a caller may capture them);
+// where the memory is not there the stages go through L.
+int stage_buffers(mrfv_ctx *ctx) {
+    if (ctx->d_W || ctx->viscous || ctx->no_stage_buffers) return MRFV_OK;
+    const size_t bytes = (size_t)ctx->cfg.slot_capacity * 5 * CELLS_P * elem_size(ctx);
+    if (hipMalloc(&ctx->d_W, bytes) != hipSuccess || hipMalloc(&ctx->d_W2, bytes) != hipSuccess) {
+        if (ctx->d_W) hipFree(ctx->d_W);
+        ctx->d_W = ctx->d_W2 = nullptr;
+        ctx->no_stage_buffers = true;
+        hipGetLastError();   // the refusal is handled here
+    }
+    return MRFV_OK;
+}
+
+// One fused stage: rhs + update over all leaves, then the jump correction on the updated
+// state.
+template <typename T>
+int do_stage_fused(mrfv_ctx *ctx, int stage, const double *dt, const T *Uin, T *Uout, T *U0,
+                   bool restrict_parents = false, double *cflmax = nullptr) {
     const HostLists &L = ctx->lists;
-    float *FF = (float *)ctx->d_FF;
+    T *FF = (T *)ctx->d_FF;
     hipEvent_t ev{};
     timing_begin(ctx, &ev);
     // the fused kernel has no grid-stride loop: its grid must cover every possible leaf
-    HIP_OK(launch_rhs_update_f32(ctx->cfg.scheme, ctx->rhs_variant, stage, dt, Uin, Uout, U0, wlist(ctx, DESC_LEAVES, 1 << 30), ctx->tb,
-                                 ctx->d_inst, FF, ctx->d_err, restrict_parents ? 1 : 0, cflmax, ctx->stream));
+    HIP_OK(launch_rhs_update<T>(flux_kernel(ctx), ctx->rhs_variant, stage, dt, Uin, Uout, U0,
+                                wlist(ctx, DESC_LEAVES, 1 << 30), ctx->tb, ctx->d_inst, FF, ctx->d_err,
+                                restrict_parents ? 1 : 0, cflmax, false, ctx->stream));
     timing_end(ctx, ev, (int64_t)L.all_leaves_cnt * CELLS_I);
     if (ctx->has_jumps) {
         for (int l = levels_to_cover(ctx) - 1; l >= 0; --l)
-            HIP_OK(launch_ff_restrict<float>(FF, wlist(ctx, desc_par(l)), ctx->tb, ctx->stream));
-        HIP_OK(launch_reflux_update<float>(stage, dt, Uout, FF, wlist(ctx, DESC_LEAVES), ctx->tb,
+            HIP_OK(launch_ff_restrict<T>(FF, wlist(ctx, desc_par(l)), ctx->tb, ctx->stream));
+        HIP_OK(launch_reflux_update<T>(stage, dt, Uout, FF, wlist(ctx, DESC_JCORR), ctx->tb,
                                            ctx->d_inst, ctx->stream));
     }
     return MRFV_OK;
@@ -336,8 +337,7 @@ int do_details_flags(mrfv_ctx *ctx, const T *U, int8_t *flags, double *det,
 // records a tree change for the next launch's gate and writes the parity's half).
 template <typename T>
 int do_adapt_device(mrfv_ctx *ctx, T *U, bool gated) {
-    const bool fused = ctx->cfg.batched && sizeof(T) == 4;
-    CALL(do_project<T>(ctx, U, false, true, fused));
+    CALL(do_project<T>(ctx, U, false, true, fused_stages(ctx)));
     CALL(do_fill<T>(ctx, U, 1 << 20, FILL_MISSING | FILL_RHO_E));
     CALL(do_details_flags<T>(ctx, U, ctx->d_flags, ctx->d_det, ctx->h_flags, ctx->h_err,
                              gated ? ctx->d_gate : nullptr));
@@ -564,6 +564,7 @@ int do_init(mrfv_ctx *ctx, mrfv_ic_fn ic, void *user, T *U) {
     }
     CALL(do_project<T>(ctx, U));
     HIP_OK(hipStreamSynchronize(ctx->stream));
+    CALL(stage_buffers(ctx));
     ctx->initialised = true;
     return MRFV_OK;
 }
@@ -585,7 +586,7 @@ int do_stages(mrfv_ctx *ctx, T *U, T *U0, T *Lb, double *dt) {
     } else {
         CALL(do_cfl<T>(ctx, U, dt));
     }
-    if (ctx->cfg.batched && sizeof(T) == 4) {
+    if (fused_stages(ctx)) {
         // fused stages, out of place through two more state buffers: U -> W -> W2 -> U;
         // parents are restricted and filled only if some leaf face reads them.  Stages
         // whose output is restricted next (W and W2 when stages read parents, U before
@@ -594,32 +595,32 @@ int do_stages(mrfv_ctx *ctx, T *U, T *U0, T *Lb, double *dt) {
         // caller, who may have written it: the first stage restricts in full, except in a
         // step graph after a step on the same tree (the last stage of an adaptive step
         // restricts, and nothing changes leaf interiors after it).
-        float *buf[4] = {(float *)U, (float *)ctx->d_W, (float *)ctx->d_W2, (float *)U};
+        T *buf[4] = {U, (T *)ctx->d_W, (T *)ctx->d_W2, U};
         const bool par = ctx->lists.parents_needed;
         bool adapt = false;
         for (const auto &p : ctx->inst) adapt = adapt || (p.adapt && p.lmax > 0);
         for (int s = 0; s < 3; ++s) {
-            float *in = buf[s], *out = buf[s + 1];
+            T *in = buf[s], *out = buf[s + 1];
             const bool skip = s > 0 || (ctx->capturing && ctx->restrict_from_stage);
-            if (par) CALL(do_project<float>(ctx, in, true, false, skip));
-            CALL(do_fill<float>(ctx, in, 1 << 20, FILL_MISSING_FACES, par));
+            if (par) CALL(do_project<T>(ctx, in, true, false, skip));
+            CALL(do_fill<T>(ctx, in, 1 << 20, FILL_MISSING_FACES, par));
             // a step graph's last stage writes the block maxima of the signal speeds for the
             // next step's CFL pass; the leaves whose boundary cells the jump correction then
             // changes get theirs again from the corrected state
             double *cflmax = ctx->capturing && s == 2 ? ctx->d_blockred : nullptr;
-            CALL(do_stage_fused(ctx, s, dt, in, out, (float *)U0, s < 2 ? par : adapt, cflmax));
+            CALL(do_stage_fused<T>(ctx, s, dt, in, out, U0, s < 2 ? par : adapt, cflmax));
             if (cflmax && ctx->has_jumps)
-                HIP_OK(launch_cfl_blocks<float>(out, wlist(ctx, DESC_JCORR), ctx->tb, ctx->d_inst,
+                HIP_OK(launch_cfl_blocks<T>(out, wlist(ctx, DESC_JCORR), ctx->tb, ctx->d_inst,
                                                 ctx->d_blockred, ctx->stream));
         }
         return MRFV_OK;
     }
-    // the viscous fluxes read the edge halos too
+    // stages through L and an update in place; the viscous fluxes read the edge halos too
     const int fill = ctx->viscous ? FILL_ALL : FILL_FACES;
     for (int s = 0; s < 3; ++s) {
         CALL(do_project<T>(ctx, U));
         CALL(do_fill<T>(ctx, U, 1 << 20, fill));
-        CALL(do_rhs<T>(ctx, U, Lb));
+        CALL(do_rhs<T>(ctx, U, Lb, true));
         CALL(do_update<T>(ctx, s, dt, U, U0, Lb));
     }
     return MRFV_OK;
@@ -929,7 +930,7 @@ int do_run(mrfv_ctx *ctx, T *U, T *U0, T *Lb, double *dt, int n, int64_t *cells)
 }
 
 // ---------------------------------------------------------- local time stepping ----
-// eq:LtsTimestep, algo:ComputeLoop, algo:Integration on the plain kernels.  A macro step
+// eq:LtsTimestep, algo:ComputeLoop, algo:Integration level by level.  A macro step
 // is 2^lmax micro steps r of dt (the eq:Cfl step of level lmax); level l completes a step
 // of its own dt_l = 2^(lmax - l) dt at micro step r when r + 1 is a multiple of
 // 2^(lmax - l).  A level's first stage is evaluated at the micro step its step starts in;
@@ -944,11 +945,10 @@ int lts_lowest_ending(int lmax, int r) { return lmax + 1 - __builtin_popcount((u
 
 template <typename T>
 int lts_buffers(mrfv_ctx *ctx) {
-    if (ctx->d_Fp && ctx->d_D) return MRFV_OK;
+    if (ctx->d_Fp && ctx->d_H0 && ctx->d_ACC) return MRFV_OK;
     HIP_OK(hipStreamSynchronize(ctx->stream));
     const size_t cap = ctx->cfg.slot_capacity, es = sizeof(T);
     struct Want { void **p; size_t bytes; } want[] = {
-        {&ctx->d_D, cap * 3 * 5 * CELLS_I * es},
         {&ctx->d_Fp, cap * 5 * CELLS_P * es},
         {&ctx->d_H0, cap * 6 * 5 * (size_t)lts_halo_slab() * es},
         {&ctx->d_ACC, cap * 6 * 5 * FACE * es}};
@@ -969,12 +969,9 @@ int do_lts_macro(mrfv_ctx *ctx, T *U, T *U0, T *Lb, double *dt, int64_t *cell_up
     CALL(lts_buffers<T>(ctx));
     const HostLists &L = ctx->lists;
     const int lmax = ctx->inst[0].lmax, top = levels_to_cover(ctx);
-    T *D = (T *)ctx->d_D, *FF = (T *)ctx->d_FF, *F = (T *)ctx->d_Fp, *H0 = (T *)ctx->d_H0,
+    T *FF = (T *)ctx->d_FF, *F = (T *)ctx->d_Fp, *H0 = (T *)ctx->d_H0,
       *ACC = (T *)ctx->d_ACC;
     const size_t cap = ctx->cfg.slot_capacity;
-    // FP32 flux divergence from the fused stage kernel (not Tait's system, which it lacks),
-    // in the context's launch shape
-    const bool fused = sizeof(T) == 4 && flux_kernel(ctx) != 4;
     int64_t cells = 0;
     for (int l = 0; l <= top; ++l) cells += (int64_t)L.leaf_cnt[l] * ((int64_t)1 << l) * CELLS_I;
     if (cell_updates) *cell_updates = cells;
@@ -989,33 +986,25 @@ int do_lts_macro(mrfv_ctx *ctx, T *U, T *U0, T *Lb, double *dt, int64_t *cell_up
         const int lo_start = r == 0 ? 0 : lts_lowest_ending(lmax, r - 1);
         for (int st = 0; st < 3; ++st) {
             const int lo_rhs = st == 0 ? lo_start : lo_end;
-            // flux divergence of the leaves being evaluated, after their copied halos; in
-            // FP32 the fused stage kernel evaluates it (reading same-level neighbours in
-            // place, so only boundary halos are filled) straight into F
+            // flux divergence of the leaves being evaluated, from the fused stage kernel (reading
+            // same-level neighbours in place, so only boundary halos are filled) into F
             for (int l = lo_rhs; l <= top; ++l) {
-                const WorkList w = wlist(ctx, desc_leaf(l));
-                if (fused) {
-                    // the boundary faces (nothing else) when some axis is not periodic
-                    if (ctx->bounded)
-                        HIP_OK(launch_fill_halos<T>(U, w, ctx->tb, (FillMode)(FILL_MISSING_FACES | FILL_PRESENT),
-                                                    ctx->stream));
-                    // (leaves without a non-leaf same-level face neighbour also write the
-                    // restriction of their L into the parent's octant of F)
-                    HIP_OK(launch_rhs_update_f32(ctx->cfg.scheme, ctx->rhs_variant, -1, dt, (const float *)U, (float *)F,
-                                                 (float *)U0, wlist(ctx, desc_leaf(l), 1 << 30), ctx->tb,
-                                                 ctx->d_inst, (float *)FF, ctx->d_err, 1, nullptr, ctx->stream));
-                    continue;
-                }
-                HIP_OK(launch_fill_halos<T>(U, w, ctx->tb, (FillMode)(FILL_FACES | FILL_PRESENT), ctx->stream));
-                HIP_OK(launch_flux<T>(flux_kernel(ctx), U, w, ctx->tb, ctx->d_inst, D, FF, ctx->stream));
-                HIP_OK(launch_lts_combine<T>(D, F, w, ctx->tb, ctx->d_inst, U, ctx->stream));
+                // the boundary faces (nothing else) when some axis is not periodic
+                if (ctx->bounded)
+                    HIP_OK(launch_fill_halos<T>(U, wlist(ctx, desc_leaf(l)), ctx->tb,
+                                                (FillMode)(FILL_MISSING_FACES | FILL_PRESENT), ctx->stream));
+                // (leaves without a non-leaf same-level face neighbour also write the
+                // restriction of their L into the parent's octant of F)
+                HIP_OK(launch_rhs_update<T>(flux_kernel(ctx), ctx->rhs_variant, RHS_TO_FIELD, dt, U, F, U0,
+                                            wlist(ctx, desc_leaf(l), 1 << 30), ctx->tb, ctx->d_inst, FF,
+                                            ctx->d_err, 1, nullptr, false, ctx->stream));
             }
-            // averaged into the parents (in FP32 the octants the fused kernel wrote are
-            // skipped: every leaf below these parents was evaluated in this stage), predicted
-            // into the jump halos
+            // averaged into the parents (the octants the fused kernel wrote are skipped: every
+            // leaf below these parents was evaluated in this stage), predicted into the jump
+            // halos
             for (int p = top - 1; p >= std::max(lo_rhs, 1) - 1; --p) {
-                if (fused && L.par_srestr[p]) continue;   // every child wrote its octant
-                HIP_OK(launch_project<T>(F, wlist(ctx, desc_par(p)), ctx->tb, ctx->stream, 31, fused));
+                if (L.par_srestr[p]) continue;   // every child wrote its octant
+                HIP_OK(launch_project<T>(F, wlist(ctx, desc_par(p)), ctx->tb, ctx->stream, 31, true));
             }
             CALL(do_fill<T>(ctx, F, 1 << 20, FILL_MISSING_FACES, true));
             // algo:Integration of the levels that end a step at r
@@ -1163,9 +1152,7 @@ int mrfv_create(mrfv_ctx **out, const mrfv_config *cfg, const mrfv_instance *ins
         }
     }
     ALLOC(ctx->d_err, sizeof(int32_t));
-    if (!(cfg->batched && cfg->dtype == MRFV_F32)) {
-        ALLOC(ctx->d_D, cap * 3 * 5 * CELLS_I * es);
-    } else {
+    if (cfg->batched && cfg->dtype == MRFV_F32) {
         ALLOC(ctx->d_W, cap * 5 * CELLS_P * es);    // second and third state buffers of the
         ALLOC(ctx->d_W2, cap * 5 * CELLS_P * es);   // fused stages
     }
@@ -1226,7 +1213,7 @@ int mrfv_destroy(mrfv_ctx *ctx) {
         for (void *p : pp)
             if (p) hipFree(p);
     }
-    void *ptrs[] = {ctx->d_inst, ctx->d_err, ctx->d_D, ctx->d_W, ctx->d_W2, ctx->d_FF, ctx->d_Fp, ctx->d_H0, ctx->d_ACC,
+    void *ptrs[] = {ctx->d_inst, ctx->d_err, ctx->d_W, ctx->d_W2, ctx->d_FF, ctx->d_Fp, ctx->d_H0, ctx->d_ACC,
                     ctx->d_blockred, ctx->d_viscred, ctx->d_bcfix, ctx->d_det, ctx->d_det4,
                     ctx->d_recheck, ctx->d_flags, ctx->d_slots, ctx->d_slots2, ctx->d_prim, ctx->tb.meta, ctx->tb.child,
                     ctx->tb.nbr, ctx->tb.lists, ctx->d_desc, ctx->d_desc_g, ctx->d_gate};
@@ -1265,8 +1252,8 @@ int mrfv_fill_halos(mrfv_ctx *ctx, void *U) {
 int mrfv_rhs_stage(mrfv_ctx *ctx, const void *U, void *L) {
     CALL(need_init(ctx));
     if (!U || !L) return fail(ctx, MRFV_EINVAL, "rhs_stage: null pointer");
-    return ctx->cfg.dtype == MRFV_F64 ? do_rhs<double>(ctx, (const double *)U, (double *)L)
-                                      : do_rhs<float>(ctx, (const float *)U, (float *)L);
+    return ctx->cfg.dtype == MRFV_F64 ? do_rhs<double>(ctx, (const double *)U, (double *)L, true)
+                                      : do_rhs<float>(ctx, (const float *)U, (float *)L, true);
 }
 
 int mrfv_rk_update(mrfv_ctx *ctx, int32_t stage, const double *dt_dev, void *U, void *U0,
@@ -1536,7 +1523,7 @@ int mrfv_fused_stage(mrfv_ctx *ctx, int32_t stage, const double *dt_dev, void *U
     const bool par = ctx->lists.parents_needed;
     if (par) CALL(do_project<float>(ctx, (float *)Uin, true));
     CALL(do_fill<float>(ctx, (float *)Uin, 1 << 20, FILL_MISSING_FACES, par));
-    return do_stage_fused(ctx, stage, dt_dev, (const float *)Uin, (float *)Uout, (float *)U0,
+    return do_stage_fused<float>(ctx, stage, dt_dev, (const float *)Uin, (float *)Uout, (float *)U0,
                           restrict_parents != 0);
 }
 
@@ -1578,12 +1565,12 @@ int mrfv_autotune(mrfv_ctx *ctx, void *U, void *U0, double *dt_dev, int32_t reps
     int best = -1;
     float best_ms = 0.f;
     for (int v = 0; v < rhs_variants(ctx->cfg.scheme); ++v) {
-        HIP_OK(launch_rhs_update_f32(ctx->cfg.scheme, v, 0, dt_dev, X, W, (float *)U0, wl, ctx->tb, ctx->d_inst,
-                                     (float *)ctx->d_FF, ctx->d_err, 0, nullptr, st));
+        HIP_OK(launch_rhs_update<float>(ctx->cfg.scheme, v, 0, dt_dev, X, W, (float *)U0, wl, ctx->tb, ctx->d_inst,
+                                     (float *)ctx->d_FF, ctx->d_err, 0, nullptr, false, st));
         HIP_OK(hipEventRecord(a, st));
         for (int r = 0; r < reps; ++r)
-            HIP_OK(launch_rhs_update_f32(ctx->cfg.scheme, v, 0, dt_dev, X, W, (float *)U0, wl, ctx->tb, ctx->d_inst,
-                                         (float *)ctx->d_FF, ctx->d_err, 0, nullptr, st));
+            HIP_OK(launch_rhs_update<float>(ctx->cfg.scheme, v, 0, dt_dev, X, W, (float *)U0, wl, ctx->tb, ctx->d_inst,
+                                         (float *)ctx->d_FF, ctx->d_err, 0, nullptr, false, st));
         HIP_OK(hipEventRecord(b, st));
         HIP_OK(hipEventSynchronize(b));
         float ms = 0.f;

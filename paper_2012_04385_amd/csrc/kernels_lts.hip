@@ -2,12 +2,10 @@
 // algo:ComputeLoop, algo:Integration).
 //
 // Level l advances with its own step dt_l = 2^(lmax - l) dt, dt being the eq:Cfl step of
-// level lmax.  Per RK stage of a level's step the host runs the plain flux kernels on the
-// leaves being evaluated, then
-//   lts_combine  the flux divergence of those leaves (from the flux kernel's differences)
-//                into the padded field F, whose parents (eq:Averaging) and halos at
-//                resolution jumps (eq:Prediction) are built by the state's own kernels
-//                (project, fill_halos) applied to F;
+// level lmax.  Per RK stage of a level's step the host runs the fused stage kernel, which
+// writes the flux divergence of the leaves being evaluated into the padded field F, whose
+// parents (eq:Averaging) and halos at resolution jumps (eq:Prediction) are built by the
+// state's own kernels (project, fill_halos) applied to F, then
 //   lts_update   the SSP-RK3 stage of the interior cells and of the halo cells of faces
 //                without a same-level neighbour (integrated with the predicted flux
 //                divergence, algo:Integration), and the stage's boundary face fluxes added
@@ -31,8 +29,6 @@ constexpr int SLAB = 3 * FACE;            // halo cells of one face that the flu
 // loads issued together) and six of the leaf's 24 face pieces (18 halo layers, 6 face-flux
 // sums), most of which are skipped: one workgroup per plane and piece took 41 % longer in
 // FP32 (27 % in FP64), most of it in starting workgroups that had little or nothing to do.
-// The combine keeps one workgroup per z-plane (with four planes each it took 7 % longer,
-// at three waves per SIMD instead of eight).
 constexpr int PLANES = 4;
 constexpr int PARTS = NI / PLANES;
 constexpr int PIECES = (6 * 3 + 6) / PARTS;
@@ -71,46 +67,6 @@ __device__ __forceinline__ bool lts_physical(const T u[5], const InstDev &P) {
     const T ke = (T)0.5 * (u[1] * u[1] + u[2] * u[2] + u[3] * u[3]) / u[0];
     const T p = (g - (T)1) * (u[4] - ke) - g * B;
     return u[0] > (T)0 && p + B > (T)0 && isfinite(u[4]) && isfinite(u[1] + u[2] + u[3]);
-}
-
-// The flux divergence of a leaf, L = -(D_x + D_y + D_z) / dx plus the gravity source of
-// eq:Euler (the plain path's combine, in the same operation order), written into the
-// padded field F.
-template <typename T>
-__global__ __launch_bounds__(TPB) void k_lts_combine(const T *__restrict__ D, T *__restrict__ F, WorkList wl,
-                                                     const BlockMeta *__restrict__ meta,
-                                                     const InstDev *__restrict__ inst,
-                                                     const T *__restrict__ U) {
-    const int nb = wl.count();
-    for (int b = blockIdx.x; b < nb; b += gridDim.x) {
-        const int slot = wl.at(b);
-        const BlockMeta mt = meta[slot];
-        const InstDev &P = inst[mt.inst];
-        const T inv_dx = (T)(1.0 / ldexp(P.dx0, -mt.level));
-        const T *Ds = D + (size_t)slot * 3 * 5 * CELLS_I;
-        const int c = blockIdx.y * TPB + threadIdx.x;
-        const int o = ((c / FACE + HW) * NP + (c / NI) % NI + HW) * NP + c % NI + HW;
-        T l[5];
-#pragma unroll
-        for (int q = 0; q < 5; ++q) {
-            const T s = (Ds[q * CELLS_I + c] + Ds[(5 + q) * CELLS_I + c]) + Ds[(10 + q) * CELLS_I + c];
-            l[q] = -s * inv_dx;
-        }
-        if (P.has_source) {   // uniform per workgroup
-            const T *ub = U + (size_t)slot * 5 * CELLS_P;
-            T u[5];
-#pragma unroll
-            for (int q = 0; q < 5; ++q) u[q] = ub[o + q * CELLS_P];
-            const T gx = (T)P.gravity[0], gy = (T)P.gravity[1], gz = (T)P.gravity[2];
-            l[1] = fma(u[0], gx, l[1]);
-            l[2] = fma(u[0], gy, l[2]);
-            l[3] = fma(u[0], gz, l[3]);
-            l[4] += fma(u[3], gz, fma(u[2], gy, u[1] * gx));
-        }
-        T *fs = F + (size_t)slot * 5 * CELLS_P;
-#pragma unroll
-        for (int q = 0; q < 5; ++q) fs[q * CELLS_P + o] = l[q];
-    }
 }
 
 // blockIdx.y = part: interior z-planes [PLANES * part, PLANES * (part + 1)) and face pieces
@@ -258,15 +214,6 @@ __global__ __launch_bounds__(TPB) void k_lts_zero(T *ACC, WorkList wl, const Blo
 }  // namespace
 
 template <typename T>
-hipError_t launch_lts_combine(const T *D, T *F, const WorkList &wl, const DevTables &tb,
-                              const InstDev *inst, const T *U, hipStream_t st) {
-    if (wl.grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_lts_combine<T>, dim3(wl.grid, NI), dim3(TPB), 0, st, D, F, wl, tb.meta,
-                       inst, U);
-    return hipGetLastError();
-}
-
-template <typename T>
 hipError_t launch_lts_update(int stage, const double *dt, T *U, T *U0, T *H0, const T *F,
                              const T *FF, T *ACC, const WorkList &wl, const DevTables &tb,
                              const InstDev *inst, int32_t *err, hipStream_t st) {
@@ -297,8 +244,6 @@ hipError_t launch_lts_zero(T *ACC, const WorkList &wl, const DevTables &tb, int 
 int lts_halo_slab() { return SLAB; }
 
 #define MRFV_LTS_INST(T)                                                                          \
-    template hipError_t launch_lts_combine<T>(const T *, T *, const WorkList &, const DevTables &, \
-                                              const InstDev *, const T *, hipStream_t);             \
     template hipError_t launch_lts_update<T>(int, const double *, T *, T *, T *, const T *,      \
                                              const T *, T *, const WorkList &, const DevTables &, \
                                              const InstDev *, int32_t *, hipStream_t);            \

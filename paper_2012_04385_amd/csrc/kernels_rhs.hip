@@ -8,11 +8,11 @@
 // WENO5.  The characteristic projection uses the closed-form left eigenvectors of the
 // Roe-averaged Jacobian (eq:StiffenedGas gives c^2 = (gamma-1)(H - |v|^2/2)).
 //
-// Work decomposition.  Plain path (k_flux): a thread walks one pencil of 16 cells along
-// one axis with a six-cell register window, so each cell's primitives are computed once
-// per pencil.  Batched path (k_rhs_update): one face per thread inside groups of z-planes,
-// fluxes staged in LDS, fused with the stage update.  Each face flux is computed once per
-// block on both paths.  Stencils are not contractions, so no MFMA is used here.
+// Work decomposition (k_rhs_update): one face per thread inside groups of z-planes, fluxes
+// staged in LDS, fused with the stage update; viscous contexts and mrfv_rhs_stage take the
+// flux divergence instead and update in a kernel of its own.  Each face flux is computed
+// once per block (slabs of a split block repeat the plane between them).  Stencils are not
+// contractions, so no MFMA is used here.
 //
 // Jump correction (algo:ComputeLoop, coarse cell adjustment): the boundary face fluxes of
 // every leaf are stored; non-leaf blocks receive the area average of their children's
@@ -30,11 +30,31 @@ namespace {
 constexpr int TPB = 256;
 
 __device__ __forceinline__ float rcp_(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ double rcp_(double x) { return 1.0 / x; }
+// FP64: the hardware's estimate (about 28 bits) and two Newton steps, 5 instructions against
+// the 11 of an IEEE division; within one unit in the last place for the normal numbers these
+// kernels meet (densities, sums of square roots, products of smoothness indicators >= 1e-24).
+__device__ __forceinline__ double rcp_(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(r, fma(-x, r, 1.0), r);
+    return fma(r, fma(-x, r, 1.0), r);
+}
 __device__ __forceinline__ float sqrt_(float x) { return __builtin_amdgcn_sqrtf(x); }
-__device__ __forceinline__ double sqrt_(double x) { return sqrt(x); }
+__device__ __forceinline__ double sqrt_(double x) {   // x >= 0, Newton on the estimate of 1/sqrt(x)
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    g = fma(fma(-g, g, x), h, g);
+    g = fma(fma(-g, g, x), h, g);
+    return x == 0.0 ? x : g;
+}
 __device__ __forceinline__ float rsqrt_(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double rsqrt_(double x) { return 1.0 / sqrt(x); }
+__device__ __forceinline__ double rsqrt_(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+}
 
 template <typename T>
 struct Gas {
@@ -54,16 +74,6 @@ struct Axes {   // physical momentum component of the rotated (n, t1, t2) triple
     static constexpr int T2 = DIR == 0 ? 3 : (DIR == 1 ? 1 : 2);
     static constexpr int STRIDE = DIR == 0 ? 1 : (DIR == 1 ? NP : NP * NP);
 };
-
-template <typename T, int DIR>
-__device__ __forceinline__ void load_state(const T *__restrict__ u, int idx, const Gas<T> &G,
-                                           CellState<T> &s) {
-    s.r = u[idx];
-    s.mn = u[idx + Axes<DIR>::N1 * CELLS_P];
-    s.mt1 = u[idx + Axes<DIR>::T1 * CELLS_P];
-    s.mt2 = u[idx + Axes<DIR>::T2 * CELLS_P];
-    s.E = u[idx + 4 * CELLS_P];
-}
 
 // Every multiply-add is an explicit fma: the compiler fuses per basic block, and this
 // code is inlined after different load paths (per-lane sources, uniform base), which
@@ -206,8 +216,8 @@ __device__ __forceinline__ T wao53(T a, T b, T c, T d, T e) {
 
 // Flux kernels of Sec. "Numerical Scheme" (the weak-scaling combinations).
 enum { SCH_ROE_WENO5 = 0, SCH_ROE_TENO5 = 1, SCH_LLF_WENO5 = 2, SCH_HLLC_WAO53 = 3 };
-// Roe-WENO5 of the barotropic system of Tait's equation (plain path only)
-constexpr int SCH_TAIT_ROE_WENO5 = 4;
+// Roe-WENO5 of the barotropic system of Tait's equation
+constexpr int SCH_TAIT_ROE_WENO5 = SCH_TAIT;
 
 // Reconstruction of the flux-splitting kernels at the right face of c.
 template <int SCH, typename T>
@@ -217,35 +227,16 @@ __device__ __forceinline__ T recon(T a, T b, T c, T d, T e) {
 }
 
 // Characteristic flux of one field: upwind by the two face cells' eigenvalues, else LLF
-// (always LLF for the LLF kernel).
-template <int SCH, typename T>
-__device__ __forceinline__ T char_flux(const T W[6], const T G[6], T lL, T lR) {
-    if (SCH != SCH_LLF_WENO5) {
-        if (lL > (T)0 && lR > (T)0) return recon<SCH>(G[0], G[1], G[2], G[3], G[4]);
-        if (lL < (T)0 && lR < (T)0) return recon<SCH>(G[5], G[4], G[3], G[2], G[1]);
-    }
-    const T al = fmax(fabs(lL), fabs(lR));
-    T gp[6], gm[6];
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-        gp[j] = (T)0.5 * (G[j] + al * W[j]);
-        gm[j] = (T)0.5 * (G[j] - al * W[j]);
-    }
-    return recon<SCH>(gp[0], gp[1], gp[2], gp[3], gp[4]) + recon<SCH>(gm[5], gm[4], gm[3], gm[2], gm[1]);
-}
-
-// Same result with at most two WENO evaluations per wavefront: if any lane of the wave
-// needs the LLF split, every lane evaluates W-(g+) + W+(g-) with g+ = g, g- = 0 for
-// upwind-right lanes and g+ = 0, g- = g for upwind-left lanes (a WENO of zeros is exactly
-// zero); otherwise one WENO with the input order picked per lane.  Equal to char_flux
-// on upwind lanes and up to rounding on LLF lanes, but mixed waves no longer execute all
-// three branches.
+// (always LLF for the LLF kernel), with at most two WENO evaluations per wavefront: if any
+// lane of the wave needs the LLF split, every lane evaluates W-(g+) + W+(g-) with g+ = g, g-
+// = 0 for upwind-right lanes and g+ = 0, g- = g for upwind-left lanes (a WENO of zeros is
+// exactly zero); otherwise one WENO with the input order picked per lane.
 // The split is formed as g+ = cp G + ap W and g- = G - g+ with per-lane coefficients
 // (cp, ap) = (1, 0) upwind-right, (0, 0) upwind-left, (1/2, a/2) LLF: g+ = (G + a W)/2
 // rounded once (halving is exact), g- = (G - a W)/2 up to rounding, and exactly G, 0 on
 // the upwind lanes.
 template <int SCH, typename T>
-__device__ __forceinline__ T char_flux_uniform(const T W[6], const T G[6], T lL, T lR) {
+__device__ __forceinline__ T char_flux(const T W[6], const T G[6], T lL, T lR) {
     const bool up = SCH != SCH_LLF_WENO5 && lL > (T)0 && lR > (T)0;
     const bool dn = SCH != SCH_LLF_WENO5 && lL < (T)0 && lR < (T)0;
     const bool llf = !(up || dn);
@@ -302,7 +293,7 @@ __device__ __forceinline__ void hllc(const T UL[5], const T UR[5], const Gas<T> 
 }
 
 // Numerical flux through the face between window cells 2 and 3 (rotated components).
-template <typename T, bool UNIFORM = false, int SCH = SCH_ROE_WENO5>
+template <int SCH, typename T>
 __device__ __forceinline__ void face_flux(const CellState<T> w[6], const Gas<T> &G, T F[5]) {
     const CellState<T> &L = w[2], &R = w[3];
     const T inv = rcp_(L.sr + R.sr);
@@ -388,20 +379,18 @@ __device__ __forceinline__ void face_flux(const CellState<T> w[6], const Gas<T> 
     // field 1: u - c
 #pragma unroll
     for (int j = 0; j < 6; ++j) { W[j] = tU[j] - xU[j]; Gc[j] = tF[j] - xF[j]; }
-#define MRFV_CF(W_, G_, a_, b_) (UNIFORM ? char_flux_uniform<SCH>(W_, G_, a_, b_) : char_flux<SCH>(W_, G_, a_, b_))
-    g[0] = MRFV_CF(W, Gc, unL - L.c, unR - R.c);
+    g[0] = char_flux<SCH>(W, Gc, unL - L.c, unR - R.c);
     // field 2: entropy, u
 #pragma unroll
     for (int j = 0; j < 6; ++j) { W[j] = fma((T)-2, tU[j], a0[j]); Gc[j] = fma((T)-2, tF[j], f0[j]); }
-    g[1] = MRFV_CF(W, Gc, unL, unR);
+    g[1] = char_flux<SCH>(W, Gc, unL, unR);
     // fields 3, 4: shear, u
-    g[2] = MRFV_CF(wt1, gt1, unL, unR);
-    g[3] = MRFV_CF(wt2, gt2, unL, unR);
+    g[2] = char_flux<SCH>(wt1, gt1, unL, unR);
+    g[3] = char_flux<SCH>(wt2, gt2, unL, unR);
     // field 5: u + c
 #pragma unroll
     for (int j = 0; j < 6; ++j) { W[j] = tU[j] + xU[j]; Gc[j] = tF[j] + xF[j]; }
-    g[4] = MRFV_CF(W, Gc, unL + L.c, unR + R.c);
-#undef MRFV_CF
+    g[4] = char_flux<SCH>(W, Gc, unL + L.c, unR + R.c);
 
     // Back to conservative components: F = R g.
     const T s15 = g[0] + g[4];
@@ -410,61 +399,6 @@ __device__ __forceinline__ void face_flux(const CellState<T> w[6], const Gas<T> 
     F[2] = v * F[0] + g[2];
     F[3] = ww * F[0] + g[3];
     F[4] = H * s15 + u * c * (g[4] - g[0]) + (T)0.5 * q2 * g[1] + v * g[2] + ww * g[3];
-}
-
-// Interior cell index (z,y,x) of pencil position p for thread coordinates (r, m).
-template <int DIR>
-__device__ __forceinline__ int cell_of(int r, int m, int p) {
-    if (DIR == 0) return (m * NI + r) * NI + p;
-    if (DIR == 1) return (m * NI + p) * NI + r;
-    return (p * NI + m) * NI + r;
-}
-
-template <int DIR>
-__device__ __forceinline__ int pencil_base(int r, int m) {
-    if (DIR == 0) return ((m + HW) * NP + (r + HW)) * NP;
-    if (DIR == 1) return ((m + HW) * NP) * NP + (r + HW);
-    return (m + HW) * NP + (r + HW);
-}
-
-// Walks the pencil (r, m) along DIR: 17 faces, flux differences for 16 cells.
-// sink.cell(q_phys, cell, dF) and sink.face(side, q_phys, F) receive the results.
-template <typename T, int DIR, int SCH, class Sink>
-__device__ __forceinline__ void pencil(const T *__restrict__ ub, int r, int m, const Gas<T> &G,
-                                       Sink &sink) {
-    constexpr int S = Axes<DIR>::STRIDE;
-    const int qmap[5] = {0, Axes<DIR>::N1, Axes<DIR>::T1, Axes<DIR>::T2, 4};
-    const int base = pencil_base<DIR>(r, m);
-    CellState<T> w[6];
-#pragma unroll
-    for (int j = 0; j < 5; ++j) {
-        load_state<T, DIR>(ub, base + (j + 1) * S, G, w[j]);
-        derive_state(G, w[j]);
-    }
-    T Fp[5];
-#pragma unroll 1
-    for (int f = 0; f <= NI; ++f) {
-        load_state<T, DIR>(ub, base + (f + 6) * S, G, w[5]);
-        derive_state(G, w[5]);
-        T F[5];
-        face_flux<T, false, SCH>(w, G, F);
-        if (f == 0) {
-#pragma unroll
-            for (int k = 0; k < 5; ++k) sink.face(2 * DIR, qmap[k], F[k]);
-        } else {
-            const int cell = cell_of<DIR>(r, m, f - 1);
-#pragma unroll
-            for (int k = 0; k < 5; ++k) sink.cell(qmap[k], cell, F[k] - Fp[k]);
-        }
-        if (f == NI) {
-#pragma unroll
-            for (int k = 0; k < 5; ++k) sink.face(2 * DIR + 1, qmap[k], F[k]);
-        }
-#pragma unroll
-        for (int k = 0; k < 5; ++k) Fp[k] = F[k];
-#pragma unroll
-        for (int j = 0; j < 5; ++j) w[j] = w[j + 1];
-    }
 }
 
 // ------------------------------------------------- Tait's equation of state --------
@@ -495,13 +429,8 @@ __device__ __forceinline__ double expm1_(double x) { return expm1(x); }
 __device__ __forceinline__ float log1p_(float x) { return log1pf(x); }
 __device__ __forceinline__ double log1p_(double x) { return log1p(x); }
 
-template <typename T, int DIR>
-__device__ __forceinline__ void load_tait(const T *__restrict__ u, int idx, const TaitGas<T> &G,
-                                          TaitState<T> &s) {
-    s.r = u[idx];
-    s.mn = u[idx + Axes<DIR>::N1 * CELLS_P];
-    s.mt1 = u[idx + Axes<DIR>::T1 * CELLS_P];
-    s.mt2 = u[idx + Axes<DIR>::T2 * CELLS_P];
+template <typename T>
+__device__ __forceinline__ void derive_state(const TaitGas<T> &G, TaitState<T> &s) {
     s.ir = rcp_(s.r);
     s.un = s.mn * s.ir;
     s.pg = pow_(s.r * G.ir0, G.g);
@@ -509,8 +438,8 @@ __device__ __forceinline__ void load_tait(const T *__restrict__ u, int idx, cons
     s.c = sqrt_(G.g * G.B * s.pg * s.ir);
 }
 
-template <typename T>
-__device__ __forceinline__ void face_flux_tait(const TaitState<T> w[6], const TaitGas<T> &G, T F[5]) {
+template <int SCH, typename T>
+__device__ __forceinline__ void face_flux(const TaitState<T> w[6], const TaitGas<T> &G, T F[5]) {
     const TaitState<T> &L = w[2], &R = w[3];
     const T sl = sqrt_(L.r), sr = sqrt_(R.r);
     const T inv = rcp_(sl + sr);
@@ -546,82 +475,27 @@ __device__ __forceinline__ void face_flux_tait(const TaitState<T> w[6], const Ta
     F[4] = (T)0;
 }
 
-// The pencil walk of `pencil` for Tait's system.
-template <typename T, int DIR, class Sink>
-__device__ __forceinline__ void pencil_tait(const T *__restrict__ ub, int r, int m, const TaitGas<T> &G,
-                                            Sink &sink) {
-    constexpr int S = Axes<DIR>::STRIDE;
-    const int qmap[5] = {0, Axes<DIR>::N1, Axes<DIR>::T1, Axes<DIR>::T2, 4};
-    const int base = pencil_base<DIR>(r, m);
-    TaitState<T> w[6];
-#pragma unroll
-    for (int j = 0; j < 5; ++j) load_tait<T, DIR>(ub, base + (j + 1) * S, G, w[j]);
-    T Fp[5];
-#pragma unroll 1
-    for (int f = 0; f <= NI; ++f) {
-        load_tait<T, DIR>(ub, base + (f + 6) * S, G, w[5]);
-        T F[5];
-        face_flux_tait<T>(w, G, F);
-        if (f == 0) {
-#pragma unroll
-            for (int k = 0; k < 5; ++k) sink.face(2 * DIR, qmap[k], F[k]);
-        } else {
-            const int cell = cell_of<DIR>(r, m, f - 1);
-#pragma unroll
-            for (int k = 0; k < 5; ++k) sink.cell(qmap[k], cell, F[k] - Fp[k]);
-        }
-        if (f == NI) {
-#pragma unroll
-            for (int k = 0; k < 5; ++k) sink.face(2 * DIR + 1, qmap[k], F[k]);
-        }
-#pragma unroll
-        for (int k = 0; k < 5; ++k) Fp[k] = F[k];
-#pragma unroll
-        for (int j = 0; j < 5; ++j) w[j] = w[j + 1];
-    }
-}
-
 template <typename T>
 __device__ __forceinline__ Gas<T> gas_of(const InstDev &P) {
     return Gas<T>{(T)P.gamma, (T)P.B, (T)(P.gamma - 1.0)};
 }
 
-// ---------------------------------------------------------------- plain path ---------
-
-template <typename T>
-struct GlobalSink {
-    T *D;      // this slot's D: [3][5][4096]
-    T *FF;     // this slot's FF: [6][5][256]
-    int dir, rm;
-    __device__ void cell(int q, int c, T v) { D[(dir * 5 + q) * CELLS_I + c] = v; }
-    __device__ void face(int side, int q, T v) { FF[(side * 5 + q) * FACE + rm] = v; }
-};
-
+// What a flux kernel works on: the equation of state and the cell record (Tait's system has
+// no energy to load).
 template <typename T, int SCH>
-__global__ __launch_bounds__(TPB) void k_flux(const T *__restrict__ U, WorkList wl,
-                                              const BlockMeta *__restrict__ meta,
-                                              const InstDev *__restrict__ inst, T *D, T *FF) {
-    const int nb = wl.count();
-    for (int b = blockIdx.x; b < nb; b += gridDim.x) {
-    const int slot = wl.at(b);
-    const int r = threadIdx.x & 15, m = threadIdx.x >> 4;
-    const T *ub = U + (size_t)slot * 5 * CELLS_P;
-    GlobalSink<T> sink{D + (size_t)slot * 3 * 5 * CELLS_I, FF + (size_t)slot * 6 * 5 * FACE,
-                       (int)blockIdx.y, m * NI + r};
-    if constexpr (SCH == SCH_TAIT_ROE_WENO5) {
-        const InstDev &P = inst[meta[slot].inst];
-        const TaitGas<T> G{(T)P.gamma, (T)P.B, (T)P.tait_A, (T)(1.0 / P.tait_rho0)};
-        if (blockIdx.y == 0) pencil_tait<T, 0>(ub, r, m, G, sink);
-        else if (blockIdx.y == 1) pencil_tait<T, 1>(ub, r, m, G, sink);
-        else pencil_tait<T, 2>(ub, r, m, G, sink);
-    } else {
-        const Gas<T> G = gas_of<T>(inst[meta[slot].inst]);
-        if (blockIdx.y == 0) pencil<T, 0, SCH>(ub, r, m, G, sink);
-        else if (blockIdx.y == 1) pencil<T, 1, SCH>(ub, r, m, G, sink);
-        else pencil<T, 2, SCH>(ub, r, m, G, sink);
+struct Phys {
+    using Eos = Gas<T>;
+    using State = CellState<T>;
+    static __device__ __forceinline__ Eos eos(const InstDev &P) { return gas_of<T>(P); }
+};
+template <typename T>
+struct Phys<T, SCH_TAIT_ROE_WENO5> {
+    using Eos = TaitGas<T>;
+    using State = TaitState<T>;
+    static __device__ __forceinline__ Eos eos(const InstDev &P) {
+        return Eos{(T)P.gamma, (T)P.B, (T)P.tait_A, (T)(1.0 / P.tait_rho0)};
     }
-    }
-}
+};
 
 // Non-leaf blocks: face-flux planes <- area average of the children's planes.
 template <typename T>
@@ -660,28 +534,31 @@ __device__ __forceinline__ int face_region(int side) {
 }
 
 // Coarse leaves at resolution jumps: replace the own boundary flux by the fine average in
-// the flux differences D (plain path).
+// the flux divergence L.
 template <typename T>
-__global__ __launch_bounds__(TPB) void k_reflux(T *D, const T *__restrict__ FF, WorkList wl,
+__global__ __launch_bounds__(TPB) void k_reflux(T *L, const T *__restrict__ FF, WorkList wl,
                                                 const BlockMeta *__restrict__ meta,
-                                                const int32_t *__restrict__ nbr) {
+                                                const int32_t *__restrict__ nbr,
+                                                const InstDev *__restrict__ inst) {
     const int nb_ = wl.count();
     for (int b = blockIdx.x; b < nb_; b += gridDim.x) {
     const int slot = wl.at(b);
+    const BlockMeta mt = meta[slot];
+    const T inv_dx = (T)(1.0 / ldexp(inst[mt.inst].dx0, -mt.level));
     const int rm = threadIdx.x, m = rm >> 4, r = rm & 15;
+    T *Ls = L + (size_t)slot * 5 * CELLS_I;
     for (int side = 0; side < 6; ++side) {
         const int nb = nbr[(size_t)slot * 27 + face_region(side)];
         if (nb < 0 || meta[nb].leaf) continue;
         const int d = side >> 1, hi = side & 1;
         const int p = hi ? NI - 1 : 0;
         const int cell = d == 0 ? (m * NI + r) * NI + p : (d == 1 ? (m * NI + p) * NI + r : (p * NI + m) * NI + r);
-        T *Dd = D + ((size_t)slot * 3 + d) * 5 * CELLS_I;
         const T *own = FF + ((size_t)slot * 6 + side) * 5 * FACE;
         const T *fine = FF + ((size_t)nb * 6 + (side ^ 1)) * 5 * FACE;
 #pragma unroll
         for (int q = 0; q < 5; ++q) {
-            const T delta = fine[q * FACE + rm] - own[q * FACE + rm];
-            Dd[q * CELLS_I + cell] += hi ? delta : -delta;
+            const T delta = (fine[q * FACE + rm] - own[q * FACE + rm]) * inv_dx;
+            Ls[q * CELLS_I + cell] += hi ? -delta : delta;
         }
         __syncthreads();
     }
@@ -697,39 +574,6 @@ __device__ __forceinline__ void add_source(const InstDev &P, const T u[5], T L[5
     L[2] = fma(u[0], gy, L[2]);
     L[3] = fma(u[0], gz, L[3]);
     L[4] += fma(u[3], gz, fma(u[2], gy, u[1] * gx));
-}
-
-template <typename T>
-__global__ __launch_bounds__(TPB) void k_combine(const T *__restrict__ D, T *L, WorkList wl,
-                                                 const BlockMeta *__restrict__ meta,
-                                                 const InstDev *__restrict__ inst,
-                                                 const T *__restrict__ U) {
-    const int nb = wl.count();
-    for (int b = blockIdx.x; b < nb; b += gridDim.x) {
-    const int slot = wl.at(b);
-    const BlockMeta mt = meta[slot];
-    const InstDev &P = inst[mt.inst];
-    const T inv_dx = (T)(1.0 / ldexp(P.dx0, -mt.level));
-    const T *Ds = D + (size_t)slot * 3 * 5 * CELLS_I;
-    T *Ls = L + (size_t)slot * 5 * CELLS_I;
-    const int c = blockIdx.y * TPB + threadIdx.x;
-    T l[5];
-#pragma unroll
-    for (int q = 0; q < 5; ++q) {
-        const T s = (Ds[q * CELLS_I + c] + Ds[(5 + q) * CELLS_I + c]) + Ds[(10 + q) * CELLS_I + c];
-        l[q] = -s * inv_dx;
-    }
-    if (P.has_source) {   // uniform per workgroup
-        const T *ub = U + (size_t)slot * 5 * CELLS_P;
-        const int o = ((c / FACE + HW) * NP + (c / NI) % NI + HW) * NP + c % NI + HW;
-        T u[5];
-#pragma unroll
-        for (int q = 0; q < 5; ++q) u[q] = ub[o + q * CELLS_P];
-        add_source(P, u, l);
-    }
-#pragma unroll
-    for (int q = 0; q < 5; ++q) Ls[q * CELLS_I + c] = l[q];
-    }
 }
 
 template <typename T>
@@ -784,18 +628,6 @@ __global__ __launch_bounds__(TPB) void k_update(int stage, const double *__restr
 
 // ---------------------------------------------------------------- batched path -------
 
-template <typename T, bool ADD>
-struct LdsSink {
-    T *acc;    // [5][4096]
-    T *FF;     // this slot's FF
-    int rm;
-    __device__ void cell(int q, int c, T v) {
-        if (ADD) acc[q * CELLS_I + c] += v;
-        else acc[q * CELLS_I + c] = v;
-    }
-    __device__ void face(int side, int q, T v) { FF[(side * 5 + q) * FACE + rm] = v; }
-};
-
 // One workgroup per leaf, or per slab of a leaf's planes where the leaves alone leave CUs idle
 // (slab_split: 8 leaves, ten steps, 3130 -> 988 us; 592 leaves with the HLLC kernel 3150 -> 2818
 // us a pass of two steps).  The block is walked in groups of GP z-planes; for each group
@@ -837,6 +669,10 @@ __host__ __device__ inline int slab_split(int nleaf, int most) {
     return 1 << best;
 }
 
+// Launch flags of the fused kernel: stencils through per-lane pointers always; cells beyond a
+// face from the own halo always (the caller filled every halo).
+enum { RHS_FORCE_PTR = 1, RHS_OWN_HALO = 2 };
+
 // Sources of one workgroup's stencils as 32-bit byte offsets from the lowest of them,
 // read through one buffer resource (range-checked: out-of-range reads return zero);
 // usable (near) when the own block and its six face neighbours lie within 4 GiB.
@@ -845,10 +681,14 @@ struct NearSrc {
     unsigned own, lo[3], hi[3];
     bool near;
 };
-constexpr int BUFFER_RSRC_WORD3 = 0x00020000;   // raw 32-bit loads (gfx9 family)
+constexpr int BUFFER_RSRC_WORD3 = 0x00020000;   // raw loads (gfx9 family)
 
-__device__ __forceinline__ float buffer_f32(__amdgpu_buffer_rsrc_t r, unsigned voff, int soff) {
-    return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, soff, 0));
+template <typename T>
+__device__ __forceinline__ T buffer_ld(__amdgpu_buffer_rsrc_t r, unsigned voff, int soff) {
+    if constexpr (sizeof(T) == 4)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, soff, 0));
+    else
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, soff, 0));
 }
 
 // Face flux along axis D for the stencil starting at padded index base (six cells at
@@ -858,21 +698,21 @@ __device__ __forceinline__ float buffer_f32(__amdgpu_buffer_rsrc_t r, unsigned v
 template <typename T, int D, int SCH, class Source>
 __device__ __forceinline__ void face_flux_at(const T *__restrict__ ub, const Source &source,
                                              const NearSrc &ns, int base, int pos0,
-                                             const Gas<T> &G, T Fp[5]) {
+                                             const typename Phys<T, SCH>::Eos &G, T Fp[5]) {
     constexpr int stride = Axes<D>::STRIDE;
     constexpr int n1 = Axes<D>::N1, t1 = Axes<D>::T1, t2 = Axes<D>::T2;   // rotated components
-    CellState<T> w[6];
-    static_assert(sizeof(T) == 4, "the fused path is FP32");
+    constexpr bool ENERGY = SCH != SCH_TAIT_ROE_WENO5;
+    typename Phys<T, SCH>::State w[6];
     constexpr int CB = CELLS_P * (int)sizeof(T);   // component stride in bytes
     if (ns.near) {
         // 32-bit offsets into one buffer resource: per-lane choice of the source block
         // only where a wavefront's stencils leave the own interior
         auto load = [&](int j, unsigned off) __attribute__((always_inline)) {
-            w[j].r = buffer_f32(ns.rsrc, off, 0);
-            w[j].mn = buffer_f32(ns.rsrc, off, n1 * CB);
-            w[j].mt1 = buffer_f32(ns.rsrc, off, t1 * CB);
-            w[j].mt2 = buffer_f32(ns.rsrc, off, t2 * CB);
-            w[j].E = buffer_f32(ns.rsrc, off, 4 * CB);
+            w[j].r = buffer_ld<T>(ns.rsrc, off, 0);
+            w[j].mn = buffer_ld<T>(ns.rsrc, off, n1 * CB);
+            w[j].mt1 = buffer_ld<T>(ns.rsrc, off, t1 * CB);
+            w[j].mt2 = buffer_ld<T>(ns.rsrc, off, t2 * CB);
+            if constexpr (ENERGY) w[j].E = buffer_ld<T>(ns.rsrc, off, 4 * CB);
         };
         if (__all(pos0 >= HW && pos0 + 5 < HW + NI)) {
 #pragma unroll
@@ -893,14 +733,19 @@ __device__ __forceinline__ void face_flux_at(const T *__restrict__ ub, const Sou
         for (int j = 0; j < 6; ++j) {
             const int pos = pos0 + j;
             const T *src = pos < HW ? lo : (pos >= HW + NI ? hi : ub);
-            load_state<T, D>(src, base + j * stride, G, w[j]);
+            const T *u = src + base + j * stride;
+            w[j].r = u[0];
+            w[j].mn = u[n1 * CELLS_P];
+            w[j].mt1 = u[t1 * CELLS_P];
+            w[j].mt2 = u[t2 * CELLS_P];
+            if constexpr (ENERGY) w[j].E = u[4 * CELLS_P];
         }
     }
     // the arithmetic follows the loads in one place for both load paths
 #pragma unroll
     for (int j = 0; j < 6; ++j) derive_state(G, w[j]);
     T F[5];
-    face_flux<T, true, SCH>(w, G, F);
+    face_flux<SCH>(w, G, F);
     Fp[0] = F[0];
     Fp[4] = F[4];
     Fp[n1] = F[1];
@@ -923,7 +768,7 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
                                                       const int32_t *__restrict__ nbr,
                                                       const InstDev *__restrict__ inst, T *FF,
                                                       int32_t *err, int restrict_parents,
-                                                      double *__restrict__ cflmax, int force_ptr) {
+                                                      double *__restrict__ cflmax, int flags) {
     constexpr int NFX = GP * NI * (NI + 1);   // x-faces per group (y-faces alike)
     // x- and y-faces are numbered with the faces 3 .. 13 of each row first: their
     // six-cell stencils lie in the own interior, so whole wavefronts of them take the
@@ -940,7 +785,9 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
     __shared__ T Fy[2][GP][NI + 1][NI][5];   // [buffer][plane][face y][x][q]
     __shared__ T Fz[NZR][NI][NI][5];         // [face plane mod NZR][y][x][q]
     __shared__ int next_chunk[2];            // per buffer: first face not yet handed out
-    __shared__ double cfl_acc[3][FACE];      // with cflmax: per owner column, the speed maxima
+    // with cflmax (FP32 only): per owner column, the speed maxima
+    __shared__ double cfl_acc[3][sizeof(T) == 4 ? FACE : 1];
+    if constexpr (sizeof(T) == 8 || SCH == SCH_TAIT_ROE_WENO5) cflmax = nullptr;
     // one workgroup per leaf, or per slab of a leaf's planes on small trees, in XCD-aware order
     // (graph launches size the grid by the slot capacity and surplus groups exit), or,
     // persistent, a fixed grid looping over them.  The last stage's CFL maxima have
@@ -954,7 +801,7 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
     const int slot = wl.at(item / nsl);
     const BlockMeta mt = meta[slot];
     const InstDev P = inst[mt.inst];   // a copy: reading it in the update cost 1.3 % on 512 leaves
-    const Gas<T> G = gas_of<T>(P);
+    const auto G = Phys<T, SCH>::eos(P);
     const T *ub = Uin + (size_t)slot * 5 * CELLS_P;
     T *ob = Uout + (size_t)slot * 5 * CELLS_P;
     // source of the cells beyond a face: the same-level neighbour shifted so that own padded
@@ -962,7 +809,7 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
     // Read again where a far workgroup needs it: twelve scalar registers less in the loop.
     auto source = [&](int side) __attribute__((always_inline)) {
         const int a = side >> 1;
-        const int n = (mt.zg >> side) & 1 ? -1 : nbr[(size_t)slot * 27 + face_region(side)];
+        const int n = ((mt.zg >> side) & 1) || (flags & RHS_OWN_HALO) ? -1 : nbr[(size_t)slot * 27 + face_region(side)];
         const int shift = NI * (a == 0 ? 1 : (a == 1 ? NP : NP * NP));
         return n >= 0 ? Uin + (size_t)n * 5 * CELLS_P + (side & 1 ? -shift : shift) : ub;
     };
@@ -979,9 +826,9 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
         }
         // every access lies below the highest source plus one block
         const uintptr_t span = mx - mn + (uintptr_t)(5 * CELLS_P * sizeof(T));
-        // force_ptr (a launch argument, so the code is the production code): always the
+        // RHS_FORCE_PTR (a launch argument, so the code is the production code): always the
         // per-lane pointer loads
-        ns.near = !force_ptr && span <= (uintptr_t)0xffffffffu;
+        ns.near = !(flags & RHS_FORCE_PTR) && span <= (uintptr_t)0xffffffffu;
         ns.rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(ub - ((uintptr_t)ub - mn) / sizeof(T)),
                                                     (short)0, ns.near ? (int)(unsigned)span : 0,
                                                     BUFFER_RSRC_WORD3);
@@ -995,7 +842,7 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
     T *ffs = FF + (size_t)slot * 6 * 5 * FACE;
     T *u0b = U0 + (size_t)slot * 5 * CELLS_I;
     const T inv_dx = (T)(1.0 / ldexp(P.dx0, -mt.level));
-    const T dtt = (T)dt[mt.inst];
+    const T dtt = stage < 0 ? (T)0 : (T)dt[mt.inst];
     const T a = stage_coef<T>(stage);
     const int tid = threadIdx.x;
     const bool owner = tid < FACE;              // column owners (x = tid & 15, y = tid >> 4)
@@ -1038,7 +885,14 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
                 lq[q] = -D[p][q] * inv_dx;
             }
             if (P.has_source) add_source(P, us, lq);   // uniform per workgroup
-            if (stage < 0) {   // flux divergence only (local time stepping): L into Uout
+            if (stage < 0) {   // flux divergence only
+                if (stage == RHS_TO_L) {   // into interiors
+                    T *lb = Uout + (size_t)slot * 5 * CELLS_I;
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) lb[q * CELLS_I + c] = lq[q];
+                    continue;
+                }
+                // RHS_TO_FIELD (local time stepping): into the padded field
 #pragma unroll
                 for (int q = 0; q < 5; ++q) {
                     ob[o + q * CELLS_P] = lq[q];
@@ -1059,7 +913,10 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
                 ob[o + q * CELLS_P] = un[q];
                 unew[p][q] = un[q];
             }
-            ok = ok && physical_state(un, G);
+            if constexpr (SCH == SCH_TAIT_ROE_WENO5)   // any positive density (the energy is not evolved)
+                ok = ok && un[0] > (T)0 && isfinite(un[1] + un[2] + un[3]);
+            else
+                ok = ok && physical_state(un, G);
             if (cflmax) {   // uniform: the last stage of a step, for the next step's CFL
                 double sp[3];
                 cfl_speeds(un[0], un[1], un[2], un[3], un[4], P.gamma, P.B, sp);
@@ -1265,22 +1122,6 @@ __global__ __launch_bounds__(TPB) void k_reflux_update(int stage, const double *
 }  // namespace
 
 template <typename T>
-hipError_t launch_flux(int scheme, const T *U, const WorkList &wl, const DevTables &tb,
-                       const InstDev *inst, T *D, T *FF, hipStream_t st) {
-    if (wl.grid <= 0) return hipSuccess;
-    const dim3 grid(wl.grid, 3), block(TPB);
-    switch (scheme) {
-        case SCH_ROE_WENO5: hipLaunchKernelGGL((k_flux<T, SCH_ROE_WENO5>), grid, block, 0, st, U, wl, tb.meta, inst, D, FF); break;
-        case SCH_ROE_TENO5: hipLaunchKernelGGL((k_flux<T, SCH_ROE_TENO5>), grid, block, 0, st, U, wl, tb.meta, inst, D, FF); break;
-        case SCH_LLF_WENO5: hipLaunchKernelGGL((k_flux<T, SCH_LLF_WENO5>), grid, block, 0, st, U, wl, tb.meta, inst, D, FF); break;
-        case SCH_HLLC_WAO53: hipLaunchKernelGGL((k_flux<T, SCH_HLLC_WAO53>), grid, block, 0, st, U, wl, tb.meta, inst, D, FF); break;
-        case SCH_TAIT_ROE_WENO5: hipLaunchKernelGGL((k_flux<T, SCH_TAIT_ROE_WENO5>), grid, block, 0, st, U, wl, tb.meta, inst, D, FF); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-template <typename T>
 hipError_t launch_ff_restrict(T *FF, const WorkList &wl, const DevTables &tb, hipStream_t st) {
     if (wl.grid <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_ff_restrict<T>, dim3(wl.grid, 6), dim3(TPB), 0, st, FF, wl, tb.child);
@@ -1288,19 +1129,10 @@ hipError_t launch_ff_restrict(T *FF, const WorkList &wl, const DevTables &tb, hi
 }
 
 template <typename T>
-hipError_t launch_reflux(T *D, const T *FF, const WorkList &wl, const DevTables &tb,
+hipError_t launch_reflux(T *L, const T *FF, const WorkList &wl, const DevTables &tb, const InstDev *inst,
                          hipStream_t st) {
     if (wl.grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_reflux<T>, dim3(wl.grid), dim3(TPB), 0, st, D, FF, wl, tb.meta, tb.nbr);
-    return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_combine(const T *D, T *L, const WorkList &wl, const DevTables &tb,
-                          const InstDev *inst, const T *U, hipStream_t st) {
-    if (wl.grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_combine<T>, dim3(wl.grid, CELLS_I / TPB), dim3(TPB), 0, st, D, L, wl,
-                       tb.meta, inst, U);
+    hipLaunchKernelGGL(k_reflux<T>, dim3(wl.grid), dim3(TPB), 0, st, L, FF, wl, tb.meta, tb.nbr, inst);
     return hipGetLastError();
 }
 
@@ -1336,21 +1168,26 @@ constexpr int persist_grid(int tpb) { return 256 * (12 / (tpb / 64) > 0 ? 12 / (
 constexpr int N_ALT_VARIANTS = 3;
 constexpr int ALT_VARIANT[N_ALT_VARIANTS] = {7, 2, 3};
 
-template <int V, int SCH>
-static void launch_variant(int stage, const double *dt, const float *Uin, float *Uout, float *U0,
-                    const WorkList &wl, const DevTables &tb, const InstDev *inst, float *FF,
-                    int32_t *err, int restrict_parents, double *cflmax, hipStream_t st) {
-    constexpr int G = RHS_GP[V], B = RHS_TPB[V];
-    constexpr bool PS = RHS_PERSIST[V];
-    constexpr int WP = RHS_WPE[V];
+template <typename T, int G, int B, bool PS, int WP, int SCH>
+static void launch_shape(int stage, const double *dt, const T *Uin, T *Uout, T *U0, const WorkList &wl,
+                         const DevTables &tb, const InstDev *inst, T *FF, int32_t *err,
+                         int restrict_parents, double *cflmax, int flags, hipStream_t st) {
     // every slab of every leaf: exactly (eager), or for any number of leaves up to the bound
     int items = wl.desc ? wl.grid : wl.n * slab_split(wl.n, 8);
     if (wl.desc)
         for (int n = 1; n <= std::min(wl.grid, SLAB_ITEMS); ++n) items = std::max(items, n * slab_split(n, 8));
     const int grid = PS ? std::min(items, persist_grid(B)) : round_xcd(items);
-    hipLaunchKernelGGL((k_rhs_update<float, G, B, PS, WP, SCH>), dim3(grid), dim3(B), 0, st, stage, dt, Uin,
-                       Uout, U0, wl, tb.meta, tb.nbr, inst, FF, err, restrict_parents, cflmax,
-                       RHS_PTR[V] ? 1 : 0);
+    hipLaunchKernelGGL((k_rhs_update<T, G, B, PS, WP, SCH>), dim3(grid), dim3(B), 0, st, stage, dt, Uin,
+                       Uout, U0, wl, tb.meta, tb.nbr, inst, FF, err, restrict_parents, cflmax, flags);
+}
+
+template <int V, int SCH>
+static void launch_variant(int stage, const double *dt, const float *Uin, float *Uout, float *U0,
+                    const WorkList &wl, const DevTables &tb, const InstDev *inst, float *FF,
+                    int32_t *err, int restrict_parents, double *cflmax, int flags, hipStream_t st) {
+    launch_shape<float, RHS_GP[V], RHS_TPB[V], RHS_PERSIST[V], RHS_WPE[V], SCH>(
+        stage, dt, Uin, Uout, U0, wl, tb, inst, FF, err, restrict_parents, cflmax,
+        flags | (RHS_PTR[V] ? RHS_FORCE_PTR : 0), st);
 }
 
 int rhs_variants(int scheme) { return scheme == SCH_ROE_WENO5 ? N_RHS_VARIANTS : N_ALT_VARIANTS; }
@@ -1370,22 +1207,45 @@ void rhs_variant_shape(int scheme, int v, int *gp, int *tpb, int *wpe, int *ptr)
 template <int SCH>
 static void launch_alt(int variant, int stage, const double *dt, const float *Uin, float *Uout,
                        float *U0, const WorkList &wl, const DevTables &tb, const InstDev *inst,
-                       float *FF, int32_t *err, int restrict_parents, double *cflmax, hipStream_t st) {
+                       float *FF, int32_t *err, int restrict_parents, double *cflmax, int flags,
+                       hipStream_t st) {
     switch (ALT_VARIANT[variant]) {
-        case 7: launch_variant<7, SCH>(stage, dt, Uin, Uout, U0, wl, tb, inst, FF, err, restrict_parents, cflmax, st); break;
-        case 2: launch_variant<2, SCH>(stage, dt, Uin, Uout, U0, wl, tb, inst, FF, err, restrict_parents, cflmax, st); break;
-        default: launch_variant<3, SCH>(stage, dt, Uin, Uout, U0, wl, tb, inst, FF, err, restrict_parents, cflmax, st); break;
+        case 7: launch_variant<7, SCH>(stage, dt, Uin, Uout, U0, wl, tb, inst, FF, err, restrict_parents, cflmax, flags, st); break;
+        case 2: launch_variant<2, SCH>(stage, dt, Uin, Uout, U0, wl, tb, inst, FF, err, restrict_parents, cflmax, flags, st); break;
+        default: launch_variant<3, SCH>(stage, dt, Uin, Uout, U0, wl, tb, inst, FF, err, restrict_parents, cflmax, flags, st); break;
     }
 }
 
-hipError_t launch_rhs_update_f32(int scheme, int variant, int stage, const double *dt, const float *Uin,
-                                 float *Uout, float *U0, const WorkList &wl, const DevTables &tb,
-                                 const InstDev *inst, float *FF, int32_t *err, int restrict_parents,
-                                 double *cflmax, hipStream_t st) {
+// FP64: one plane per group, so that two workgroups' faces fit the LDS; 256 threads of up to
+// 256 registers each.
+constexpr int F64_GP = 1, F64_TPB = 256;
+
+template <typename T>
+hipError_t launch_rhs_update(int scheme, int variant, int stage, const double *dt, const T *Uin,
+                             T *Uout, T *U0, const WorkList &wl, const DevTables &tb,
+                             const InstDev *inst, T *FF, int32_t *err, int restrict_parents,
+                             double *cflmax, bool own_halo, hipStream_t st) {
     if (wl.grid <= 0) return hipSuccess;
     if (Uin == Uout) return hipErrorInvalidValue;   // neighbours' interiors are read
+    if (stage == RHS_TO_L && restrict_parents) return hipErrorInvalidValue;
+    const int flags = own_halo ? RHS_OWN_HALO : 0;
+#define MRFV_ARGS stage, dt, Uin, Uout, U0, wl, tb, inst, FF, err, restrict_parents, cflmax, flags, st
+    if constexpr (sizeof(T) == 8) {
+        switch (scheme) {
+            case SCH_ROE_WENO5: launch_shape<T, F64_GP, F64_TPB, false, 1, SCH_ROE_WENO5>(MRFV_ARGS); break;
+            case SCH_ROE_TENO5: launch_shape<T, F64_GP, F64_TPB, false, 1, SCH_ROE_TENO5>(MRFV_ARGS); break;
+            case SCH_LLF_WENO5: launch_shape<T, F64_GP, F64_TPB, false, 1, SCH_LLF_WENO5>(MRFV_ARGS); break;
+            case SCH_HLLC_WAO53: launch_shape<T, F64_GP, F64_TPB, false, 1, SCH_HLLC_WAO53>(MRFV_ARGS); break;
+            case SCH_TAIT_ROE_WENO5: launch_shape<T, F64_GP, F64_TPB, false, 1, SCH_TAIT_ROE_WENO5>(MRFV_ARGS); break;
+            default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    } else {
+    if (scheme == SCH_TAIT_ROE_WENO5) {
+        launch_shape<T, 2, 512, false, 1, SCH_TAIT_ROE_WENO5>(MRFV_ARGS);
+        return hipGetLastError();
+    }
     if (variant < 0 || variant >= rhs_variants(scheme)) return hipErrorInvalidValue;
-#define MRFV_ARGS stage, dt, Uin, Uout, U0, wl, tb, inst, FF, err, restrict_parents, cflmax, st
     switch (scheme) {
         case SCH_ROE_WENO5:
             switch (variant) {
@@ -1410,8 +1270,9 @@ hipError_t launch_rhs_update_f32(int scheme, int variant, int stage, const doubl
         case SCH_HLLC_WAO53: launch_alt<SCH_HLLC_WAO53>(variant, MRFV_ARGS); break;
         default: return hipErrorInvalidValue;
     }
-#undef MRFV_ARGS
     return hipGetLastError();
+    }
+#undef MRFV_ARGS
 }
 
 template <typename T>
@@ -1425,14 +1286,13 @@ hipError_t launch_reflux_update(int stage, const double *dt, T *U, const T *FF,
 }
 
 #define MRFV_INST_RHS(T)                                                                    \
-    template hipError_t launch_flux<T>(int, const T *, const WorkList &, const DevTables &, \
-                                       const InstDev *, T *, T *, hipStream_t);             \
+    template hipError_t launch_rhs_update<T>(int, int, int, const double *, const T *, T *, T *, \
+                                             const WorkList &, const DevTables &, const InstDev *, \
+                                             T *, int32_t *, int, double *, bool, hipStream_t); \
     template hipError_t launch_ff_restrict<T>(T *, const WorkList &, const DevTables &,     \
                                               hipStream_t);                                 \
     template hipError_t launch_reflux<T>(T *, const T *, const WorkList &, const DevTables &, \
-                                         hipStream_t);                                      \
-    template hipError_t launch_combine<T>(const T *, T *, const WorkList &, const DevTables &, \
-                                          const InstDev *, const T *, hipStream_t);         \
+                                         const InstDev *, hipStream_t);                     \
     template hipError_t launch_update<T>(int, const double *, T *, T *, const T *,          \
                                          const WorkList &, const DevTables &, const InstDev *, \
                                          int32_t *, hipStream_t);                           \

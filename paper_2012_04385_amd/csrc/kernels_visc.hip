@@ -9,13 +9,13 @@
 // the face, the tangential ones the mean of the two cells' central differences; v_face is
 // the mean of the two velocities.
 //
-// k_visc runs after the convective flux kernel of the plain path and subtracts the viscous
-// flux differences from its per-direction differences D and the boundary face fluxes from
-// its face planes FF, so that the jump correction averages total fluxes.  It walks the
+// k_visc runs after the convective flux kernel and adds the divergence of the viscous flux to
+// its flux divergence L and subtracts the boundary face fluxes from its face planes FF, so
+// that the jump correction averages total fluxes.  It walks the
 // z-planes of a leaf with the velocities of three planes in LDS (coalesced row loads, one
 // division per cell and plane pass) and evaluates all three face directions there.  The
 // tangential neighbours of the halo cells beside the faces lie in the edge halo regions,
-// which the plain path fills for viscous contexts.
+// which viscous contexts fill.
 //
 // k_rinv_block / k_visc_dt: the explicit bound of the viscous terms.  Fourier analysis of
 // the central operator gives -(40/3) nu / dx^2 for the most negative eigenvalue of the
@@ -144,7 +144,7 @@ __device__ __forceinline__ void load_plane(const T *__restrict__ ub, VisLds<T> &
 template <typename T>
 __global__ __launch_bounds__(TPB) void k_visc(const T *__restrict__ U, WorkList wl,
                                               const BlockMeta *__restrict__ meta,
-                                              const InstDev *__restrict__ inst, T *D, T *FF) {
+                                              const InstDev *__restrict__ inst, T *Lr, T *FF) {
     __shared__ VisLds<T> L;
     const int nb = wl.count();
     const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
@@ -157,11 +157,18 @@ __global__ __launch_bounds__(TPB) void k_visc(const T *__restrict__ U, WorkList 
         const T mu = (T)P.mu, inv_dx = (T)(1.0 / ldexp(P.dx0, -mt.level));
         const bool energy = P.eos == 0;
         const T *ub = U + (size_t)slot * 5 * CELLS_P;
-        T *Ds = D + (size_t)slot * 3 * 5 * CELLS_I;
+        T *Ls = Lr + (size_t)slot * 5 * CELLS_I;
         T *Fs = FF + (size_t)slot * 6 * 5 * FACE;
         load_plane(ub, L, z0s - 1, tid);
         load_plane(ub, L, z0s, tid);
-        T Fz[5];   // the z-face below the current plane
+        T Fz[5];    // the z-face below the current plane
+        T dxy[4];   // x and y differences of the plane below, waiting for its upper z-face
+        // one read-modify-write of L per cell: the sum over the three directions
+        auto add = [&](int z, const T (&dz)[4]) {
+            const int cell = (z * NI + ty) * NI + tx;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) Ls[(1 + k) * CELLS_I + cell] += (dxy[k] + dz[k]) * inv_dx;
+        };
 #pragma unroll 1
         for (int z = z0s; z < z1s; ++z) {
             load_plane(ub, L, z + 1, tid);
@@ -217,10 +224,12 @@ __global__ __launch_bounds__(TPB) void k_visc(const T *__restrict__ U, WorkList 
                 if (z == 0) {
 #pragma unroll
                     for (int k = 1; k < 5; ++k) Fs[(4 * 5 + k) * FACE + rm] -= Fn[k];
-                } else if (z > z0s) {   // the slab's first face only starts the carry
-                    const int cell = ((z - 1) * NI + ty) * NI + tx;
+                }
+                if (z > z0s) {   // the slab's first face only starts the carry
+                    T dz[4];
 #pragma unroll
-                    for (int k = 1; k < 5; ++k) Ds[(2 * 5 + k) * CELLS_I + cell] -= Fn[k] - Fz[k];
+                    for (int k = 0; k < 4; ++k) dz[k] = Fn[1 + k] - Fz[1 + k];
+                    add(z - 1, dz);
                 }
 #pragma unroll
                 for (int k = 0; k < 5; ++k) Fz[k] = Fn[k];
@@ -240,21 +249,21 @@ __global__ __launch_bounds__(TPB) void k_visc(const T *__restrict__ U, WorkList 
                     hi.n_hi = vat(L, zp, 2, tx, ty + 1) - vat(L, zp, 2, tx, ty - 1);
                     hi.hi_hi = vat(L, zp, 1, tx, ty + 1) - vat(L, zp, 1, tx, ty - 1);
                     visc_flux<T, 2>(lo, hi, mu, inv_dx, energy, Fn);
-                    const int cell = (z * NI + ty) * NI + tx;
 #pragma unroll
                     for (int k = 1; k < 5; ++k) {
-                        Ds[(2 * 5 + k) * CELLS_I + cell] -= Fn[k] - Fz[k];
+                        Fz[k] = Fn[k] - Fz[k];   // the last plane's z difference, added below
                         if (z == NI - 1) Fs[(5 * 5 + k) * FACE + rm] -= Fn[k];
                     }
                 }
             }
             __syncthreads();
             // x and y differences of the cell, boundary face planes of the x and y sides
-            const int cell = (z * NI + ty) * NI + tx;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                Ds[(0 * 5 + 1 + k) * CELLS_I + cell] -= L.fx[k][ty][tx + 1] - L.fx[k][ty][tx];
-                Ds[(1 * 5 + 1 + k) * CELLS_I + cell] -= L.fy[k][ty + 1][tx] - L.fy[k][ty][tx];
+            for (int k = 0; k < 4; ++k)
+                dxy[k] = (L.fx[k][ty][tx + 1] - L.fx[k][ty][tx]) + (L.fy[k][ty + 1][tx] - L.fy[k][ty][tx]);
+            if (z == z1s - 1) {
+                const T dz[4] = {Fz[1], Fz[2], Fz[3], Fz[4]};
+                add(z, dz);
             }
             if (tx == 0 || tx == NI - 1) {   // x-face planes: r = y, m = z
                 const int side = tx == 0 ? 0 : 1, f = tx == 0 ? 0 : NI;
@@ -325,9 +334,9 @@ __global__ __launch_bounds__(TPB) void k_visc_dt(WorkList leaves, const int32_t 
 
 template <typename T>
 hipError_t launch_visc(const T *U, const WorkList &wl, const DevTables &tb, const InstDev *inst,
-                       T *D, T *FF, hipStream_t st) {
+                       T *L, T *FF, hipStream_t st) {
     if (wl.grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_visc<T>, dim3(wl.grid, VSLABS), dim3(TPB), 0, st, U, wl, tb.meta, inst, D, FF);
+    hipLaunchKernelGGL(k_visc<T>, dim3(wl.grid, VSLABS), dim3(TPB), 0, st, U, wl, tb.meta, inst, L, FF);
     return hipGetLastError();
 }
 

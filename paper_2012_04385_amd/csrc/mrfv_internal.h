@@ -268,13 +268,13 @@ hipError_t static_totals_scratch(int device, double **ptr);
 template <typename T>
 hipError_t launch_cfl_blocks(const T *U, const WorkList &wl, const DevTables &tb,
                              const InstDev *inst, double *blockmax, hipStream_t st);
-// Viscous terms (kernels_visc.hip): the viscous flux subtracted from the plain flux
-// kernel's differences D and face planes FF of the listed leaves, and the viscous bound on
+// Viscous terms (kernels_visc.hip): the divergence of the viscous flux added to L and the
+// flux subtracted from the face planes FF of the listed leaves, and the viscous bound on
 // the time step (dt[inst] = min(dt[inst], cfl 3/16 dx_lmax^2 / (mu max 1/rho))) for the
 // instances with mu > 0; blockmax: one double per leaf.
 template <typename T>
 hipError_t launch_visc(const T *U, const WorkList &wl, const DevTables &tb, const InstDev *inst,
-                       T *D, T *FF, hipStream_t st);
+                       T *L, T *FF, hipStream_t st);
 template <typename T>
 hipError_t launch_visc_dt(const T *U, const WorkList &leaves, const DevTables &tb,
                           const InstDev *inst, int n_inst, double *blockmax, double *dt,
@@ -284,34 +284,34 @@ hipError_t launch_totals(const T *U, const WorkList &leaves, const DevTables &tb
                          const InstDev *inst, int n_inst, double *blocksum, double *tot,
                          hipStream_t st);
 template <typename T>
-hipError_t launch_flux(int scheme, const T *U, const WorkList &leaves, const DevTables &tb,
-                       const InstDev *inst, T *D, T *FF, hipStream_t st);
-template <typename T>
 hipError_t launch_ff_restrict(T *FF, const WorkList &parents, const DevTables &tb,
                               hipStream_t st);
 template <typename T>
-hipError_t launch_reflux(T *D, const T *FF, const WorkList &leaves, const DevTables &tb,
-                         hipStream_t st);
-template <typename T>
-hipError_t launch_combine(const T *D, T *L, const WorkList &leaves, const DevTables &tb,
-                          const InstDev *inst, const T *U, hipStream_t st);
+hipError_t launch_reflux(T *L, const T *FF, const WorkList &leaves, const DevTables &tb,
+                         const InstDev *inst, hipStream_t st);
 template <typename T>
 hipError_t launch_update(int stage, const double *dt, T *U, T *U0, const T *L,
                          const WorkList &leaves, const DevTables &tb, const InstDev *inst,
                          int32_t *err, hipStream_t st);
 // Fused stage: reads the state from Uin (same-level neighbours' interiors directly, the
 // own halo elsewhere) and writes the new interior state to Uout != Uin.
-// scheme: flux kernel (mrfv_scheme); variant: launch shape index in [0, rhs_variants(scheme))
-// (all give the same result).
+// scheme: flux kernel (mrfv_scheme, or SCH_TAIT); variant: launch shape index in [0,
+// rhs_variants(scheme)) (all give the same result; FP64 and Tait's system have one shape).
 // restrict_parents: leaves with meta.srestr also write the restriction of their new state
 // (all components) into their parent's octant of Uout.
-// stage < 0: no update; Uout (a padded field) receives the interior flux divergence
+// stage RHS_TO_FIELD: no update; Uout (a padded field) receives the interior flux divergence
 // L = -sum_d dF_d / dx + S (local time stepping), and with restrict_parents its
-// restriction into the parents' octants of Uout; U0 is not touched, cflmax must be null.
-hipError_t launch_rhs_update_f32(int scheme, int variant, int stage, const double *dt, const float *Uin,
-                                 float *Uout, float *U0, const WorkList &leaves, const DevTables &tb,
-                                 const InstDev *inst, float *FF, int32_t *err, int restrict_parents,
-                                 double *cflmax, hipStream_t st);   // cflmax: null, or CFL block maxima out
+// restriction into the parents' octants of Uout.  RHS_TO_L: the same into an interiors-only
+// array (restrict_parents 0).  Neither touches U0 or dt; cflmax must be null.
+// own_halo: cells beyond every face come from the own halo (all filled by the caller).
+// cflmax: null, or CFL block maxima out (FP32 only).
+constexpr int RHS_TO_FIELD = -1, RHS_TO_L = -2;
+constexpr int SCH_TAIT = 4;
+template <typename T>
+hipError_t launch_rhs_update(int scheme, int variant, int stage, const double *dt, const T *Uin,
+                             T *Uout, T *U0, const WorkList &leaves, const DevTables &tb,
+                             const InstDev *inst, T *FF, int32_t *err, int restrict_parents,
+                             double *cflmax, bool own_halo, hipStream_t st);
 int rhs_variants(int scheme);
 int rhs_default_variant(int scheme);   // the shape fastest on the measured trees
 void rhs_variant_shape(int scheme, int v, int *gp, int *tpb, int *wpe, int *ptr);
@@ -322,9 +322,6 @@ hipError_t launch_reflux_update(int stage, const double *dt, T *U, const T *FF,
 // Local time stepping (kernels_lts.hip).  F: padded flux divergence [cap][5][24^3];
 // H0: stage-start state of the halo cells of jump faces [cap][6][5][lts_halo_slab()];
 // ACC: time-integrated boundary face fluxes [cap][6][5][16][16] (the layout of FF).
-template <typename T>
-hipError_t launch_lts_combine(const T *D, T *F, const WorkList &leaves, const DevTables &tb,
-                              const InstDev *inst, const T *U, hipStream_t st);
 template <typename T>
 hipError_t launch_lts_update(int stage, const double *dt, T *U, T *U0, T *H0, const T *F,
                              const T *FF, T *ACC, const WorkList &leaves, const DevTables &tb,
@@ -366,7 +363,7 @@ struct mrfv_ctx {
     int32_t *d_err = nullptr;          // device error word
     void *d_W = nullptr, *d_W2 = nullptr;   // second and third padded state buffers
                                             // (fused FP32 stages: U -> W -> W2 -> U)
-    void *d_D = nullptr;               // flux differences [cap][3][5][16^3]
+    bool no_stage_buffers = false;     // W and W2 could not be had: stages go through L
     void *d_FF = nullptr;              // boundary face fluxes [cap][6][5][16][16]
     void *d_Fp = nullptr, *d_H0 = nullptr, *d_ACC = nullptr;   // local time stepping, on first use
     double *d_blockred = nullptr;      // [cap][5] per-block partial reductions
@@ -423,7 +420,7 @@ struct mrfv_ctx {
     int lists_cap = 0;
     // kernel timing
     bool has_jumps = false;            // some leaf has a non-leaf same-level face neighbour
-    bool viscous = false;              // some instance has mu > 0 (plain path only)
+    bool viscous = false;              // some instance has mu > 0 (stages through L)
     bool bounded = false;              // some instance has a non-periodic axis
     bool capturing = false;            // recording a step graph
     // step graphs: the CFL pass takes the block maxima the previous step wrote after its
