@@ -130,6 +130,7 @@ WorkList wlist(const mrfv_ctx *ctx, int which, int grid_cap = 2048, bool gated =
         int64_t bound = ctx->cfg.slot_capacity;
         if (which >= desc_lvl(0) && which < desc_lvl(0) + DESC_PER_LEVEL * MAX_LEVELS)   // per-level lists
             bound = std::min<int64_t>(bound, ctx->lvl_bound[(which - desc_lvl(0)) / DESC_PER_LEVEL]);
+        w.n = d[2 * which + 1];
         w.grid = (int)std::min<int64_t>(bound, grid_cap);
     } else {
         const std::vector<int32_t> &d = ctx->lists.desc;
@@ -631,14 +632,15 @@ int do_stages(mrfv_ctx *ctx, T *U, T *U0, T *Lb, double *dt) {
 // read their work lists through the gated device descriptors, so one capture serves every
 // later tree.  Captured on the library's own stream, launched on the caller's.
 // Which launches a captured step graph contains: the finest level present, whether
-// resolution jumps exist, and which per-level lists are non-empty.  Counts and list
+// resolution jumps exist, which per-level lists are non-empty, and the fused kernel's split
+// of the leaves over workgroups.  Counts and list
 // contents are read on the device, so one graph serves every tree with the same key.
 GraphKey graph_key(const mrfv_ctx *ctx) {
     const HostLists &L = ctx->lists;
     uint64_t k = (uint64_t)L.max_level | ((uint64_t)ctx->has_jumps << 4) |
                  ((uint64_t)L.parents_needed << 63) | ((uint64_t)ctx->cfl_from_stage << 62) |
                  ((uint64_t)ctx->restrict_from_stage << 61) | ((uint64_t)L.pars_copy_only << 60);
-    uint64_t k2 = 0;
+    uint64_t k2 = (uint64_t)rhs_slabs(L.all_leaves_cnt) << (3 * MAX_LEVELS);   // <= 8
     for (int l = 0; l <= L.max_level && l < MAX_LEVELS; ++l) {
         if (L.desc[2 * desc_par(l) + 1] > 0) k |= 1ull << (5 + l);
         if (L.desc[2 * desc_jleaf(l) + 1] > 0) k |= 1ull << (5 + MAX_LEVELS + l);

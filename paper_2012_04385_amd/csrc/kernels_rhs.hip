@@ -127,7 +127,9 @@ __device__ __forceinline__ T weno5(T a, T b, T c, T d, T e) {
         // The fourth powers of the indicators leave the FP32 range once they pass ~1e9
         // (steep characteristic fluxes behind strong shocks, LLF splits): the weights are
         // homogeneous of degree zero in (e0, e1, e2), so such lanes evaluate them again
-        // with the indicators scaled by their maximum.  Other lanes are unchanged.
+        // with the indicators scaled by their maximum.  Other lanes are unchanged.  (One
+        // check per field, with a second copy of the evaluation behind it, spilled registers
+        // and took 5 % longer.)
         if (!isfinite(r)) {
             const T sc = rcp_(fmax(e0, fmax(e1, e2)));
             r = weno5_combine(e0 * sc, e1 * sc, e2 * sc, h0, h1, h2, c);
@@ -255,7 +257,8 @@ __device__ __forceinline__ T char_flux(const T W[6], const T G[6], T lL, T lR) {
         gp[j] = fma(ap, W[j], cp * G[j]);
         gm[j] = G[j] - gp[j];
     }
-    return recon<SCH>(gp[0], gp[1], gp[2], gp[3], gp[4]) + recon<SCH>(gm[5], gm[4], gm[3], gm[2], gm[1]);
+    return recon<SCH>(gp[0], gp[1], gp[2], gp[3], gp[4]) +
+           recon<SCH>(gm[5], gm[4], gm[3], gm[2], gm[1]);
 }
 
 // HLLC flux (Toro, Spruce & Speares 1994) between two rotated conservative states
@@ -652,21 +655,21 @@ constexpr int NFZ = NI * NI;                  // z-faces per face plane (256)
 // planes and starts and drains its own pipeline (taken as 500 faces).  The split with the
 // least of that is taken, the smaller on ties: 8 leaves go to 64 workgroups, 592
 // leaves (three on the fullest CU) to 1184, 512 leaves (two on every CU) and large trees
-// stay whole.  Split launches have at most SLAB_ITEMS workgroups, so a graph's grid is bounded.
+// stay whole.  FP64 workgroups fill their CU alone (pairs = false).  Split launches have at most SLAB_ITEMS workgroups, which bounds the grid of a
+// captured one (a step graph's key holds the split of the tree it is launched for).
 constexpr int SLAB_ITEMS = 4096;
-__host__ __device__ inline int slab_split(int nleaf, int most) {
+int slab_split(int nleaf, int most, bool pairs) {
     if (nleaf > SLAB_ITEMS / 2) return 1;
-    int best = 0, best_t = 0;
-    for (int b = 0; b < 4; ++b) {   // 2^b slabs
-        if ((1 << b) > most || (nleaf << b) > SLAB_ITEMS) break;
-        const int load = ((nleaf << b) + 255) >> 8;
-        const int t = (73 * (load & ~1) + 93 * (load & 1)) * ((8 * 1600 >> b) + 256 + 500);
-        if (b == 0 || t < best_t) {
-            best = b;
+    int best = 1, best_t = 0;
+    for (int n = 1; n <= most && n * nleaf <= SLAB_ITEMS; n *= 2) {
+        const int load = (nleaf * n + 255) / 256;
+        const int t = (pairs ? 73 * (load & ~1) + 93 * (load & 1) : 93 * load) * (8 * 1600 / n + 256 + 500);
+        if (n == 1 || t < best_t) {
+            best = n;
             best_t = t;
         }
     }
-    return 1 << best;
+    return best;
 }
 
 // Launch flags of the fused kernel: stencils through per-lane pointers always; cells beyond a
@@ -760,7 +763,7 @@ constexpr int rhs_waves(int wpe, int gp, int tpb) { return wpe == 1 && gp <= 2 &
 
 template <typename T, int GP, int TPB_F, bool PERSIST, int WPE, int SCH>
 __global__ __attribute__((amdgpu_flat_work_group_size(TPB_F, TPB_F),
-                          amdgpu_waves_per_eu(PERSIST ? WPE : rhs_waves(WPE, GP, TPB_F))))
+                          amdgpu_waves_per_eu(PERSIST || sizeof(T) == 8 ? WPE : rhs_waves(WPE, GP, TPB_F))))
 void k_rhs_update(int stage, const double *__restrict__ dt,
                                                       const T *__restrict__ Uin, T *__restrict__ Uout,
                                                       T *U0, WorkList wl,
@@ -768,23 +771,32 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
                                                       const int32_t *__restrict__ nbr,
                                                       const InstDev *__restrict__ inst, T *FF,
                                                       int32_t *err, int restrict_parents,
-                                                      double *__restrict__ cflmax, int flags) {
+                                                      double *__restrict__ cflmax, int flags,
+                                                      int nsl) {
     constexpr int NFX = GP * NI * (NI + 1);   // x-faces per group (y-faces alike)
     // x- and y-faces are numbered with the faces 3 .. 13 of each row first: their
     // six-cell stencils lie in the own interior, so whole wavefronts of them take the
     // uniform-base loads of face_flux_at; the faces 0-2 and 14-16 follow
     constexpr int NF_IN = NI - 5, NF_OUT = NI + 1 - NF_IN;
     constexpr int NFX_IN = GP * NI * NF_IN;
-    // Groups are pipelined: while the column owners update group g from one buffer, all
-    // wavefronts compute the faces of group g + 1 into the other, taking 64-face chunks
-    // from an LDS counter (owners join after their update); one barrier per group.
+    // Groups are pipelined without barriers.  The slab's faces form one queue of 64-face
+    // chunks, group after group, which the wavefronts take from an LDS counter; the four
+    // wavefronts of column owners update a group as soon as its faces are in LDS, between two
+    // chunks.  A group's faces go to buffer g & 1, so a chunk of group g starts only after
+    // the owners have updated group g - 2.  Everything a wavefront waits for comes from
+    // earlier in the queue, and a wavefront that waits still runs its own due updates, so
+    // the earliest unfinished item never waits: no deadlock.  (One barrier per group, 25
+    // chunks on eight wavefronts, left 40 % of the wavefronts' time waiting.)
     // z-face planes live in a ring of 2 GP + 1 slots (face plane kf in slot kf mod NZR):
     // the planes of group g (k0 .. k0 + GP) and those group g + 1 adds never share a slot.
+    // The x- (and y-) faces of a group leave a part chunk; those of two consecutive groups
+    // share one.
     constexpr int NZR = 2 * GP + 1;
     __shared__ T Fx[2][GP][NI][NI + 1][5];   // [buffer][plane][y][face x][q]
     __shared__ T Fy[2][GP][NI + 1][NI][5];   // [buffer][plane][face y][x][q]
     __shared__ T Fz[NZR][NI][NI][5];         // [face plane mod NZR][y][x][q]
-    __shared__ int next_chunk[2];            // per buffer: first face not yet handed out
+    constexpr int NGRP = NI / GP;
+    __shared__ int next_chunk, faces_done[NGRP], owners_done[NGRP];   // queue head; per group
     // with cflmax (FP32 only): per owner column, the speed maxima
     __shared__ double cfl_acc[3][sizeof(T) == 4 ? FACE : 1];
     if constexpr (sizeof(T) == 8 || SCH == SCH_TAIT_ROE_WENO5) cflmax = nullptr;
@@ -793,8 +805,6 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
     // persistent, a fixed grid looping over them.  The last stage's CFL maxima have
     // CFL_SLABS places per leaf.
     const int nleaf = wl.count();
-    constexpr int NGRP = NI / GP, MAX_SLABS = NGRP < 8 ? NGRP : 8;
-    const int nsl = slab_split(nleaf, cflmax ? min(MAX_SLABS, CFL_SLABS) : MAX_SLABS);
     auto block = [&](int item) __attribute__((always_inline)) {
     const int slab = item & (nsl - 1);
     const int g_lo = slab * (NGRP / nsl), g_hi = g_lo + NGRP / nsl;   // this workgroup's groups
@@ -944,75 +954,95 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
         }
     };
 
-    // faces of group g: x-faces (plane p, row y, face f), y-faces (plane p, face f,
-    // column x), then the z-face planes the group adds (all GP + 1 for the slab's first group)
-    auto group_faces = [&](int g) {
-        const int k0 = g * GP;
-        const int first_z = g == g_lo ? 0 : 1;
-        const int total = 2 * NFX + (GP + 1 - first_z) * NFZ;
-        const int buf = g & 1;
-        const int lane = tid & 63;
-        for (;;) {
-            int c0 = 0;
-            if (lane == 0) c0 = atomicAdd(&next_chunk[buf], 64);
-            c0 = __shfl(c0, 0);
-            if (c0 >= total) break;
-            const int t = c0 + lane;
-            if (t >= total) continue;
-            T F[5];
-            if (t < NFX) {
-                int f, y, p;
-                if (t < NFX_IN) {               // faces 3 .. 13 first: stencils in the interior
-                    f = 3 + t % NF_IN;
-                    y = (t / NF_IN) % NI;
-                    p = t / (NF_IN * NI);
-                } else {
-                    const int v = t - NFX_IN, fb = v % NF_OUT;
-                    f = fb < 3 ? fb : fb + NF_IN;
-                    y = (v / NF_OUT) % NI;
-                    p = v / (NF_OUT * NI);
-                }
-                const int base = ((k0 + p + HW) * NP + y + HW) * NP + f + 1;
-                face_flux_at<T, 0, SCH>(ub, source, ns, base, f + 1, G, F);
-#pragma unroll
-                for (int q = 0; q < 5; ++q) Fx[buf][p][y][f][q] = F[q];
-                if (f == 0 || f == NI) {
-#pragma unroll
-                    for (int q = 0; q < 5; ++q) ffs[((f ? 1 : 0) * 5 + q) * FACE + (k0 + p) * NI + y] = F[q];
-                }
-            } else if (t < 2 * NFX) {
-                const int u = t - NFX;
-                int x, f, p;
-                if (u < NFX_IN) {
-                    x = u % NI;
-                    f = 3 + (u / NI) % NF_IN;
-                    p = u / (NI * NF_IN);
-                } else {
-                    const int v = u - NFX_IN, fb = (v / NI) % NF_OUT;
-                    x = v % NI;
-                    f = fb < 3 ? fb : fb + NF_IN;
-                    p = v / (NI * NF_OUT);
-                }
-                const int base = ((k0 + p + HW) * NP + f + 1) * NP + x + HW;
-                face_flux_at<T, 1, SCH>(ub, source, ns, base, f + 1, G, F);
-#pragma unroll
-                for (int q = 0; q < 5; ++q) Fy[buf][p][f][x][q] = F[q];
-                if (f == 0 || f == NI) {
-#pragma unroll
-                    for (int q = 0; q < 5; ++q) ffs[((2 + (f ? 1 : 0)) * 5 + q) * FACE + (k0 + p) * NI + x] = F[q];
-                }
+    // The queue: the z-faces below the slab (4 chunks), then per pair of groups the first
+    // group's x-, y- and z-faces, the shared part chunks of x and y, the second group's.
+    constexpr int NFULL = NFX / 64, REM = NFX % 64, NMERGED = REM ? 2 : 0;
+    constexpr int CHUNKS = 2 * NFULL + 4 * GP;                 // whole chunks of a group
+    constexpr int PAIR = 2 * CHUNKS + NMERGED;
+    static_assert(NFZ == 256 && (REM == 0 || 64 / REM >= 2), "chunk layout");
+    const int ngrp = g_hi - g_lo;
+    const int total = 4 + (ngrp >> 1) * PAIR + (ngrp & 1) * (CHUNKS + NMERGED);
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    struct Chunk {
+        int axis, g, i;       // i: 64-face chunk of the group's axis, or -1: the shared part
+        bool below;           // the z-faces below the slab
+    };
+    auto decode = [&](int c) {
+        if (c < 4) return Chunk{2, g_lo, c, true};
+        c -= 4;
+        const int pr = c / PAIR, r = c - pr * PAIR;
+        int g = g_lo + 2 * pr, k = r;
+        if (r >= CHUNKS) {
+            if (r < CHUNKS + NMERGED) return Chunk{r - CHUNKS, g, -1, false};
+            g += 1;
+            k = r - CHUNKS - NMERGED;
+        }
+        if (k < NFULL) return Chunk{0, g, k, false};
+        if (k < 2 * NFULL) return Chunk{1, g, k - NFULL, false};
+        return Chunk{2, g, k - 2 * NFULL, false};
+    };
+    // Evaluates a chunk: x-faces (plane p, row y, face f), y-faces (plane p, face f, column
+    // x), z-face planes.
+    auto chunk_faces = [&](const Chunk &ch) {
+        int g = ch.g, t = 64 * ch.i + lane;
+        if (REM && ch.i < 0) {   // lanes h * REM ..: the part chunk of group g + h
+            const int h = lane / (REM ? REM : 64);
+            t = 64 * NFULL + lane - h * REM;
+            g += h;
+            if (h >= 2 || g >= g_hi) return;
+        }
+        const int k0 = g * GP, buf = g & 1;
+        T F[5];
+        if (ch.axis == 0) {
+            int f, y, p;
+            if (t < NFX_IN) {               // faces 3 .. 13 first: stencils in the interior
+                f = 3 + t % NF_IN;
+                y = (t / NF_IN) % NI;
+                p = t / (NF_IN * NI);
             } else {
-                const int u = t - 2 * NFX;
-                const int x = u % NI, y = (u / NI) % NI, j = u / NFZ + first_z;
-                const int kf = k0 + j;          // face between interior planes kf-1 and kf
-                const int base = ((kf + 1) * NP + y + HW) * NP + x + HW;   // padded z = kf+1 .. kf+6
-                face_flux_at<T, 2, SCH>(ub, source, ns, base, kf + 1, G, F);
+                const int v = t - NFX_IN, fb = v % NF_OUT;
+                f = fb < 3 ? fb : fb + NF_IN;
+                y = (v / NF_OUT) % NI;
+                p = v / (NF_OUT * NI);
+            }
+            const int base = ((k0 + p + HW) * NP + y + HW) * NP + f + 1;
+            face_flux_at<T, 0, SCH>(ub, source, ns, base, f + 1, G, F);
 #pragma unroll
-                for (int q = 0; q < 5; ++q) Fz[kf % NZR][y][x][q] = F[q];
-                if (kf == 0 || kf == NI) {
+            for (int q = 0; q < 5; ++q) Fx[buf][p][y][f][q] = F[q];
+            if (f == 0 || f == NI) {
 #pragma unroll
-                    for (int q = 0; q < 5; ++q) ffs[((4 + (kf ? 1 : 0)) * 5 + q) * FACE + y * NI + x] = F[q];
-                }
+                for (int q = 0; q < 5; ++q) ffs[((f ? 1 : 0) * 5 + q) * FACE + (k0 + p) * NI + y] = F[q];
+            }
+        } else if (ch.axis == 1) {
+            int x, f, p;
+            if (t < NFX_IN) {
+                x = t % NI;
+                f = 3 + (t / NI) % NF_IN;
+                p = t / (NI * NF_IN);
+            } else {
+                const int v = t - NFX_IN, fb = (v / NI) % NF_OUT;
+                x = v % NI;
+                f = fb < 3 ? fb : fb + NF_IN;
+                p = v / (NI * NF_OUT);
+            }
+            const int base = ((k0 + p + HW) * NP + f + 1) * NP + x + HW;
+            face_flux_at<T, 1, SCH>(ub, source, ns, base, f + 1, G, F);
+#pragma unroll
+            for (int q = 0; q < 5; ++q) Fy[buf][p][f][x][q] = F[q];
+            if (f == 0 || f == NI) {
+#pragma unroll
+                for (int q = 0; q < 5; ++q) ffs[((2 + (f ? 1 : 0)) * 5 + q) * FACE + (k0 + p) * NI + x] = F[q];
+            }
+        } else {
+            const int x = t % NI, y = (t / NI) % NI;
+            const int kf = k0 + t / NFZ + (ch.below ? 0 : 1);   // face between interior planes kf-1 and kf
+            const int base = ((kf + 1) * NP + y + HW) * NP + x + HW;   // padded z = kf+1 .. kf+6
+            face_flux_at<T, 2, SCH>(ub, source, ns, base, kf + 1, G, F);
+#pragma unroll
+            for (int q = 0; q < 5; ++q) Fz[kf % NZR][y][x][q] = F[q];
+            if (kf == 0 || kf == NI) {
+#pragma unroll
+                for (int q = 0; q < 5; ++q) ffs[((4 + (kf ? 1 : 0)) * 5 + q) * FACE + y * NI + x] = F[q];
             }
         }
     };
@@ -1031,21 +1061,61 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
         update_group(k0, D);
     };
 
-    if (tid < 2) next_chunk[tid] = 0;
+    if (tid == 0) next_chunk = 0;
+    if (tid < NGRP) faces_done[tid] = owners_done[tid] = 0;
     if (cflmax && owner)
 #pragma unroll
         for (int d = 0; d < 3; ++d) cfl_acc[d][tid] = 0.0;
     __syncthreads();
-    // iteration g: update group g (g >= g_lo) and compute the faces of group g + 1
+    auto reached = [&](int *count, int n) {
+        const bool r = __builtin_amdgcn_readfirstlane(
+                           __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) >= n;
+        if (r) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        return r;
+    };
+    auto signal = [&](int *count) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        if (lane == 0) __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    {
+        int u = wave < FACE / 64 ? g_lo : g_hi;   // the next group this wavefront updates
+        int held = -1;                            // the chunk taken from the queue
+        bool more = true;
 #pragma unroll 1
-    for (int g = g_lo - 1; g < g_hi; ++g) {
-        if (g >= g_lo && owner) group_update(g);
-        if (g + 1 < g_hi) group_faces(g + 1);
-        // group g's counter is free again (its faces were done before the last barrier);
-        // group g + 2 takes it after the next one
-        if (g >= g_lo && tid == 0) next_chunk[g & 1] = 0;
-        __syncthreads();
+        for (;;) {
+            if (u < g_hi && reached(&faces_done[u], CHUNKS + NMERGED + (u == g_lo ? 4 : 0))) {
+                group_update(u);
+                signal(&owners_done[u]);
+                ++u;
+                continue;
+            }
+            if (held < 0 && more) {
+                int c = 0;
+                if (lane == 0) c = __hip_atomic_fetch_add(&next_chunk, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                held = __builtin_amdgcn_readfirstlane(c);
+                if (held >= total) {
+                    held = -1;
+                    more = false;
+                }
+            }
+            if (held >= 0) {
+                const Chunk ch = decode(held);
+                const bool shared = ch.i < 0 && ch.g + 1 < g_hi;   // writes group g + 1 too
+                const int need = ch.g - 2 + (shared ? 1 : 0);
+                if (need < g_lo || reached(&owners_done[need], FACE / 64)) {
+                    chunk_faces(ch);
+                    signal(&faces_done[ch.g]);
+                    if (shared) signal(&faces_done[ch.g + 1]);
+                    held = -1;
+                    continue;
+                }
+            } else if (u >= g_hi) {
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
     }
+    if constexpr (PERSIST) __syncthreads();   // the counters start again for the next block
     if (!ok) atomicOr(err, 1);
     if (cflmax) {
         // maxima of the signal speeds (the CFL pass's values, stored as the maxima of the first
@@ -1168,17 +1238,21 @@ constexpr int persist_grid(int tpb) { return 256 * (12 / (tpb / 64) > 0 ? 12 / (
 constexpr int N_ALT_VARIANTS = 3;
 constexpr int ALT_VARIANT[N_ALT_VARIANTS] = {7, 2, 3};
 
+int rhs_slabs(int nleaf) { return slab_split(nleaf, 8, true); }
+
 template <typename T, int G, int B, bool PS, int WP, int SCH>
 static void launch_shape(int stage, const double *dt, const T *Uin, T *Uout, T *U0, const WorkList &wl,
                          const DevTables &tb, const InstDev *inst, T *FF, int32_t *err,
                          int restrict_parents, double *cflmax, int flags, hipStream_t st) {
-    // every slab of every leaf: exactly (eager), or for any number of leaves up to the bound
-    int items = wl.desc ? wl.grid : wl.n * slab_split(wl.n, 8);
-    if (wl.desc)
-        for (int n = 1; n <= std::min(wl.grid, SLAB_ITEMS); ++n) items = std::max(items, n * slab_split(n, 8));
+    // every slab of every leaf: exactly (eager), or (captured) for any number of leaves with
+    // this split up to the list's bound
+    constexpr int MAX_SLABS = std::min(NI / G, 8);
+    const int nsl = slab_split(wl.n, cflmax ? std::min(MAX_SLABS, CFL_SLABS) : MAX_SLABS, sizeof(T) == 4);
+    const int items = !wl.desc ? wl.n * nsl : nsl == 1 ? wl.grid : std::min(wl.grid, SLAB_ITEMS / nsl) * nsl;
     const int grid = PS ? std::min(items, persist_grid(B)) : round_xcd(items);
     hipLaunchKernelGGL((k_rhs_update<T, G, B, PS, WP, SCH>), dim3(grid), dim3(B), 0, st, stage, dt, Uin,
-                       Uout, U0, wl, tb.meta, tb.nbr, inst, FF, err, restrict_parents, cflmax, flags);
+                       Uout, U0, wl, tb.meta, tb.nbr, inst, FF, err, restrict_parents, cflmax, flags,
+                       nsl);
 }
 
 template <int V, int SCH>
@@ -1216,9 +1290,11 @@ static void launch_alt(int variant, int stage, const double *dt, const float *Ui
     }
 }
 
-// FP64: one plane per group, so that two workgroups' faces fit the LDS; 256 threads of up to
-// 256 registers each.
-constexpr int F64_GP = 1, F64_TPB = 256;
+// FP64: two planes per group and 512 threads, whose faces fill the LDS of a CU (138 KB) and
+// whose 219 registers leave two waves per SIMD.  Two workgroups of 256 threads with one plane
+// per group took 4 % longer on 2304 leaves and 16 % on 15 (a shear layer's step 6.12 against
+// 5.88 ms); three waves per SIMD spill 156 registers (10.6 ms).
+constexpr int F64_GP = 2, F64_TPB = 512;
 
 template <typename T>
 hipError_t launch_rhs_update(int scheme, int variant, int stage, const double *dt, const T *Uin,

@@ -66,7 +66,7 @@ struct DevTables {
 struct WorkList {
     const int32_t *base = nullptr;   // device list array
     const int32_t *desc = nullptr;   // device {offset, count}, or null
-    int32_t off = 0, n = 0;          // host offset and count when desc is null
+    int32_t off = 0, n = 0;          // host offset and count (with desc: the count at capture)
     int grid = 0;                    // workgroups to launch (0: skip the launch)
     __device__ __forceinline__ int count() const { return desc ? desc[1] : n; }
     __device__ __forceinline__ int32_t at(int i) const { return base[(desc ? desc[0] : off) + i]; }
@@ -312,6 +312,7 @@ hipError_t launch_rhs_update(int scheme, int variant, int stage, const double *d
                              T *Uout, T *U0, const WorkList &leaves, const DevTables &tb,
                              const InstDev *inst, T *FF, int32_t *err, int restrict_parents,
                              double *cflmax, bool own_halo, hipStream_t st);
+int rhs_slabs(int nleaf);   // workgroups per leaf of a launch over nleaf leaves
 int rhs_variants(int scheme);
 int rhs_default_variant(int scheme);   // the shape fastest on the measured trees
 void rhs_variant_shape(int scheme, int v, int *gp, int *tpb, int *wpe, int *ptr);
