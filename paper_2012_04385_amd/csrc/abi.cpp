@@ -130,6 +130,8 @@ WorkList wlist(const mrfv_ctx *ctx, int which, int grid_cap = 2048, bool gated =
         int64_t bound = ctx->cfg.slot_capacity;
         if (which >= desc_lvl(0) && which < desc_lvl(0) + DESC_PER_LEVEL * MAX_LEVELS)   // per-level lists
             bound = std::min<int64_t>(bound, ctx->lvl_bound[(which - desc_lvl(0)) / DESC_PER_LEVEL]);
+        for (int l = 0; l < MAX_LEVELS; ++l)
+            if (which == desc_fitem(l)) bound *= 26;   // items
         w.n = d[2 * which + 1];
         w.grid = (int)std::min<int64_t>(bound, grid_cap);
     } else {
@@ -186,20 +188,18 @@ int do_fill(mrfv_ctx *ctx, T *U, int max_level, int mode = FILL_ALL, bool with_p
         HIP_OK(launch_fill_halos<T>(U, wlist(ctx, DESC_PARS, 1024), ctx->tb, (FillMode)(FILL_ALL | qsel),
                                     ctx->stream));
     for (int l = 0; l <= std::min(max_level, levels_to_cover(ctx)); ++l) {
-        if (m == FILL_ALL) {
+        if (m == FILL_MISSING_FACES) {
+            // a stage: the parents' regions its predictions read and the leaves' faces
+            HIP_OK(launch_fill_halos<T>(U, wlist(ctx, desc_fitem(l), 4096), ctx->tb, (FillMode)(FILL_ITEMS | qsel), ctx->stream));
+        } else if (m == FILL_ALL) {
             HIP_OK(launch_fill_halos<T>(U, wlist(ctx, desc_lvl(l), 1024), ctx->tb, (FillMode)mode,
                                         ctx->stream));
         } else {
-            // a stage fills only the parents its predictions read; the fill before the
-            // details (FILL_MISSING) all non-leaf blocks, whose details are judged too
-            // (of those only the halo regions the predictions read)
-            const int pw = m == FILL_MISSING_FACES ? desc_pfill(l) : desc_par(l);
-            const int pm = m == FILL_MISSING_FACES ? FILL_MASKED : 0;
+            // (the fill before the details takes all non-leaf blocks: theirs are judged too)
             if (with_parents && !merged)
-                HIP_OK(launch_fill_halos<T>(U, wlist(ctx, pw, 1024), ctx->tb, (FillMode)(FILL_ALL | qsel | pm),
+                HIP_OK(launch_fill_halos<T>(U, wlist(ctx, desc_par(l), 1024), ctx->tb, (FillMode)(FILL_ALL | qsel),
                                             ctx->stream));
-            const int which = m == FILL_FACES ? desc_leaf(l)
-                              : m == FILL_MISSING_FACES ? desc_jleaf(l) : desc_jleaf26(l);
+            const int which = m == FILL_FACES ? desc_leaf(l) : desc_jleaf26(l);
             HIP_OK(launch_fill_halos<T>(U, wlist(ctx, which, 1024), ctx->tb, (FillMode)mode, ctx->stream));
         }
     }
@@ -264,7 +264,7 @@ int do_rhs(mrfv_ctx *ctx, const T *U, T *Lout, bool own_halo) {
         HIP_OK(launch_visc<T>(U, wlist(ctx, DESC_LEAVES), ctx->tb, ctx->d_inst, Lout, FF, ctx->stream));
     if (ctx->has_jumps) {
         for (int l = L.max_level - 1; l >= 0; --l)
-            HIP_OK(launch_ff_restrict<T>(FF, wlist(ctx, desc_par(l)), ctx->tb, ctx->stream));
+            HIP_OK(launch_ff_restrict<T>(FF, wlist(ctx, desc_ffr(l)), ctx->tb, ctx->stream));
         HIP_OK(launch_reflux<T>(Lout, FF, wlist(ctx, DESC_JCORR), ctx->tb, ctx->d_inst, ctx->stream));
     }
     return MRFV_OK;
@@ -312,7 +312,7 @@ int do_stage_fused(mrfv_ctx *ctx, int stage, const double *dt, const T *Uin, T *
     timing_end(ctx, ev, (int64_t)L.all_leaves_cnt * CELLS_I);
     if (ctx->has_jumps) {
         for (int l = levels_to_cover(ctx) - 1; l >= 0; --l)
-            HIP_OK(launch_ff_restrict<T>(FF, wlist(ctx, desc_par(l)), ctx->tb, ctx->stream));
+            HIP_OK(launch_ff_restrict<T>(FF, wlist(ctx, desc_ffr(l)), ctx->tb, ctx->stream));
         HIP_OK(launch_reflux_update<T>(stage, dt, Uout, FF, wlist(ctx, DESC_JCORR), ctx->tb,
                                            ctx->d_inst, ctx->stream));
     }
@@ -643,10 +643,10 @@ GraphKey graph_key(const mrfv_ctx *ctx) {
     uint64_t k2 = (uint64_t)rhs_slabs(L.all_leaves_cnt) << (3 * MAX_LEVELS);   // <= 8
     for (int l = 0; l <= L.max_level && l < MAX_LEVELS; ++l) {
         if (L.desc[2 * desc_par(l) + 1] > 0) k |= 1ull << (5 + l);
-        if (L.desc[2 * desc_jleaf(l) + 1] > 0) k |= 1ull << (5 + MAX_LEVELS + l);
-        if (L.desc[2 * desc_pfill(l) + 1] > 0) k |= 1ull << (5 + 2 * MAX_LEVELS + l);
+        if (L.desc[2 * desc_fitem(l) + 1] > 0) k |= 1ull << (5 + MAX_LEVELS + l);
         if (L.desc[2 * desc_pproj(l) + 1] > 0) k |= 1ull << (5 + 3 * MAX_LEVELS + l);
         if (L.desc[2 * desc_jleaf26(l) + 1] > 0) k2 |= 1ull << l;   // the adaptation's fill
+        if (L.desc[2 * desc_ffr(l) + 1] > 0) k2 |= 1ull << (44 + l);
         if (L.par_srestr[l]) k2 |= 1ull << (MAX_LEVELS + l);            // restriction passes
         if (L.pproj_srestr[l]) k2 |= 1ull << (2 * MAX_LEVELS + l);      // left out
     }
@@ -1015,7 +1015,7 @@ int do_lts_macro(mrfv_ctx *ctx, T *U, T *U0, T *Lb, double *dt, int64_t *cell_up
                                             ctx->d_inst, ctx->d_err, ctx->stream));
             if (st == 2 && ctx->has_jumps) {
                 for (int p = top - 1; p >= lo_end; --p)
-                    HIP_OK(launch_ff_restrict<T>(ACC, wlist(ctx, desc_par(p)), ctx->tb, ctx->stream));
+                    HIP_OK(launch_ff_restrict<T>(ACC, wlist(ctx, desc_ffr(p)), ctx->tb, ctx->stream));
                 for (int l = lo_end; l <= top; ++l)
                     HIP_OK(launch_lts_adjust<T>(U, ACC, wlist(ctx, desc_leaf(l)), ctx->tb, ctx->d_inst,
                                                 ctx->stream));
@@ -1089,7 +1089,8 @@ int mrfv_create(mrfv_ctx **out, const mrfv_config *cfg, const mrfv_instance *ins
         return bail(MRFV_EHIP);
     }
     const size_t cap = cfg->slot_capacity, es = elem_size(ctx);
-    ctx->lists_cap = 2 * cfg->n_instances + 10 * cfg->slot_capacity + 16;
+    // lists of blocks (at most 9 per block) and fill items (26 per parent, 6 per leaf)
+    ctx->lists_cap = 2 * cfg->n_instances + 19 * cfg->slot_capacity + 64;
     ctx->prim_batch = 128;
     ctx->lvl_bound.assign(MAX_LEVELS, 0);
     for (int i = 0; i < cfg->n_instances; ++i) {

@@ -13,7 +13,7 @@
 //                faces a coarse cell adjustment reads);
 //   lts_adjust   the coarse cell adjustment at the end of a coarse leaf's step: on faces
 //                whose same-level neighbour is refined, the own time-integrated flux is
-//                replaced by the area average of the fine sums (built by k_ff_restrict);
+//                replaced by the area average of the fine sums;
 //   lts_zero     sums that a coarse leaf has used start again.
 // All kernels are memory-bound streams over whole blocks: one workgroup per block part,
 // coalesced along x.
@@ -161,8 +161,9 @@ template <typename T>
 __global__ __launch_bounds__(TPB) void k_lts_adjust(T *U, const T *__restrict__ ACC, WorkList wl,
                                                     const BlockMeta *__restrict__ meta,
                                                     const int32_t *__restrict__ nbr,
+                                                    const int32_t *__restrict__ child,
                                                     const InstDev *__restrict__ inst) {
-    const int nb_ = wl.count();
+    const int nb_ = wl.count(), q = blockIdx.y;   // a component per workgroup
     const int rm = threadIdx.x;
     for (int b = blockIdx.x; b < nb_; b += gridDim.x) {
         const int slot = wl.at(b);
@@ -173,14 +174,11 @@ __global__ __launch_bounds__(TPB) void k_lts_adjust(T *U, const T *__restrict__ 
             const int nb = nbr[(size_t)slot * 27 + face_region(side)];
             if (nb < 0 || meta[nb].leaf) continue;   // uniform per workgroup
             const int d = side >> 1, hi = side & 1;
-            const T *own = ACC + ((size_t)slot * 6 + side) * 5 * FACE;
-            const T *fine = ACC + ((size_t)nb * 6 + (side ^ 1)) * 5 * FACE;
-#pragma unroll
-            for (int q = 0; q < 5; ++q) {
-                const int n = plane_cell(q, d, hi ? HW + NI - 1 : HW, rm >> 4, rm & 15);
-                const T o = own[q * FACE + rm], fn = fine[q * FACE + rm];
-                ub[n] += hi ? (o - fn) / dx : (fn - o) / dx;
-            }
+            const int n = plane_cell(q, d, hi ? HW + NI - 1 : HW, rm >> 4, rm & 15);
+            const T o = ACC[(((size_t)slot * 6 + side) * 5 + q) * FACE + rm];
+            const T fn = fine_face(ACC, child, nb, side ^ 1, q, rm >> 4, rm & 15);
+            ub[n] += hi ? (o - fn) / dx : (fn - o) / dx;
+            __syncthreads();   // sides share edge cells
         }
     }
 }
@@ -227,8 +225,8 @@ template <typename T>
 hipError_t launch_lts_adjust(T *U, const T *ACC, const WorkList &wl, const DevTables &tb,
                              const InstDev *inst, hipStream_t st) {
     if (wl.grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_lts_adjust<T>, dim3(wl.grid), dim3(TPB), 0, st, U, ACC, wl, tb.meta, tb.nbr,
-                       inst);
+    hipLaunchKernelGGL(k_lts_adjust<T>, dim3(wl.grid, 5), dim3(TPB), 0, st, U, ACC, wl, tb.meta, tb.nbr,
+                       tb.child, inst);
     return hipGetLastError();
 }
 

@@ -106,11 +106,10 @@ struct Region {
                     // boundary has fixed values: the region then holds those values
 };
 
-__device__ __forceinline__ Region make_region(int mode, int ridx, int zg) {
+__device__ __forceinline__ Region make_region(bool faces, int ridx, int zg) {
     Region g;
     g.mirbits = 0;
     int r[3];
-    const bool faces = (mode & FILL_FACES) != 0;
     if (!faces) {
         const int reg = ridx < 13 ? ridx : ridx + 1;
         r[0] = reg % 3 - 1;
@@ -184,17 +183,20 @@ __global__ __launch_bounds__(TPB) void k_fill_halos(T *__restrict__ U, WorkList 
     const int nb = wl.count();
     const int tid = threadIdx.x;
     const int nreg = (mode & FILL_FACES) ? 6 : 26;
-    // blocks in XCD-aware order, as in k_details
+    // blocks (or items: a block and a region) in XCD-aware order, as in k_details
+    const bool items = (mode & FILL_ITEMS) != 0;
     for (int base = 0; base < nb; base += gridDim.x) {
         const int m_round = min(nb - base, (int)gridDim.x);
         const int bi = xcd_item(blockIdx.x, gridDim.x, m_round);
         if (bi >= m_round) continue;   // uniform per workgroup
-        const int slot = wl.at(base + bi);
+        const int entry = wl.at(base + bi);
+        const int slot = items ? entry >> 5 : entry;
+        const bool faces = items ? (entry & 31) >= 26 : (mode & FILL_FACES) != 0;
+        const int item_reg = faces ? (entry & 31) - 26 : entry & 31;
         const BlockMeta m = meta[slot];
-        // regions blockIdx.y, blockIdx.y + gridDim.y, ... of the block
-        for (int ridx = blockIdx.y; ridx < nreg; ridx += gridDim.y) {
-            if ((mode & FILL_MASKED) && !((m.pmask >> ridx) & 1)) continue;   // not read
-            const Region g = make_region(mode, ridx, EXT ? m.zg : (m.zg & 63));
+        // regions blockIdx.y, blockIdx.y + gridDim.y, ... of the block, or the item's
+        for (int ridx = items ? item_reg : blockIdx.y; ridx < (items ? item_reg + 1 : nreg); ridx += gridDim.y) {
+            const Region g = make_region(faces, ridx, EXT ? m.zg : (m.zg & 63));
             // mirrored axes as bits (no run-time indexing into the region's arrays, which would
             // put them in scratch memory)
             const int mirbits = EXT ? g.mirbits : 0;
@@ -956,11 +958,13 @@ template <typename T>
 hipError_t launch_fill_halos(T *U, const WorkList &wl, const DevTables &tb, FillMode mode,
                              hipStream_t st) {
     if (wl.grid <= 0) return hipSuccess;
-    // one workgroup per region, except in the mode before the details (all 26 regions of
+    // one workgroup per region (a stage's fill: per item, so that none starts for a region
+    // that is read in place and one launch covers a level's parents and leaves), except in
+    // the mode before the details (all 26 regions of
     // the jump leaves, most of them read in place and skipped): two per block, 13 regions
     // each (0.42 -> 0.38 ms per step of config 5; one workgroup per block in the stages'
     // missing-faces mode measured no faster)
-    const int nreg = (mode & FILL_FACES) ? 6 : 26;
+    const int nreg = (mode & FILL_ITEMS) ? 1 : (mode & FILL_FACES) ? 6 : 26;
     const int gy = ((mode & FILL_MISSING) && !(mode & FILL_FACES)) ? 2 : nreg;
     const dim3 grid = grid2(round_xcd(wl.grid), gy);
     if (tb.ext_bc)

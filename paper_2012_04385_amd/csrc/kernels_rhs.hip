@@ -15,9 +15,9 @@
 // contractions, so no MFMA is used here.
 //
 // Jump correction (algo:ComputeLoop, coarse cell adjustment): the boundary face fluxes of
-// every leaf are stored; non-leaf blocks receive the area average of their children's
-// (k_ff_restrict), and a coarse leaf next to a non-leaf same-level neighbour replaces its
-// own boundary flux by that average.  With one global dt per step the correction is
+// every leaf are stored, and a coarse leaf next to a non-leaf same-level neighbour replaces
+// its own boundary flux by the area average of that neighbour's children's (which hold
+// their children's average where they are not leaves: k_ff_restrict).  With one global dt per step the correction is
 // applied at every stage.
 #include <algorithm>
 
@@ -537,13 +537,17 @@ __device__ __forceinline__ int face_region(int side) {
 }
 
 // Coarse leaves at resolution jumps: replace the own boundary flux by the fine average in
-// the flux divergence L.
+// the flux divergence L.  One workgroup per leaf and component (a thread's chain is then one
+// value per side; with all five components 47 us per launch on 1188 leaves), the average
+// taken from the children in place: restricting every parent's planes first took five
+// launches a stage on six levels.
 template <typename T>
 __global__ __launch_bounds__(TPB) void k_reflux(T *L, const T *__restrict__ FF, WorkList wl,
                                                 const BlockMeta *__restrict__ meta,
                                                 const int32_t *__restrict__ nbr,
+                                                const int32_t *__restrict__ child,
                                                 const InstDev *__restrict__ inst) {
-    const int nb_ = wl.count();
+    const int nb_ = wl.count(), q = blockIdx.y;
     for (int b = blockIdx.x; b < nb_; b += gridDim.x) {
     const int slot = wl.at(b);
     const BlockMeta mt = meta[slot];
@@ -556,13 +560,9 @@ __global__ __launch_bounds__(TPB) void k_reflux(T *L, const T *__restrict__ FF, 
         const int d = side >> 1, hi = side & 1;
         const int p = hi ? NI - 1 : 0;
         const int cell = d == 0 ? (m * NI + r) * NI + p : (d == 1 ? (m * NI + p) * NI + r : (p * NI + m) * NI + r);
-        const T *own = FF + ((size_t)slot * 6 + side) * 5 * FACE;
-        const T *fine = FF + ((size_t)nb * 6 + (side ^ 1)) * 5 * FACE;
-#pragma unroll
-        for (int q = 0; q < 5; ++q) {
-            const T delta = (fine[q * FACE + rm] - own[q * FACE + rm]) * inv_dx;
-            Ls[q * CELLS_I + cell] += hi ? -delta : delta;
-        }
+        const T own = FF[(((size_t)slot * 6 + side) * 5 + q) * FACE + rm];
+        const T delta = (fine_face(FF, child, nb, side ^ 1, q, m, r) - own) * inv_dx;
+        Ls[q * CELLS_I + cell] += hi ? -delta : delta;
         __syncthreads();
     }
     }
@@ -1159,8 +1159,9 @@ __global__ __launch_bounds__(TPB) void k_reflux_update(int stage, const double *
                                                        T *U, const T *__restrict__ FF, WorkList wl,
                                                        const BlockMeta *__restrict__ meta,
                                                        const int32_t *__restrict__ nbr,
+                                                       const int32_t *__restrict__ child,
                                                        const InstDev *__restrict__ inst) {
-    const int nb_ = wl.count();
+    const int nb_ = wl.count(), q = blockIdx.y;   // as k_reflux
     for (int b = blockIdx.x; b < nb_; b += gridDim.x) {
     const int slot = wl.at(b);
     const BlockMeta mt = meta[slot];
@@ -1176,14 +1177,10 @@ __global__ __launch_bounds__(TPB) void k_reflux_update(int stage, const double *
         const int o = d == 0 ? ((m + HW) * NP + r + HW) * NP + p
                              : (d == 1 ? ((m + HW) * NP + p) * NP + r + HW
                                        : (p * NP + m + HW) * NP + r + HW);
-        const T *own = FF + ((size_t)slot * 6 + side) * 5 * FACE;
-        const T *fine = FF + ((size_t)nb * 6 + (side ^ 1)) * 5 * FACE;
-#pragma unroll
-        for (int q = 0; q < 5; ++q) {
-            const T delta = fine[q * FACE + rm] - own[q * FACE + rm];
-            // L changes by -(D_new - D)/dx with D_new - D = +delta (high) / -delta (low)
-            ub[o + q * CELLS_P] += coef * (hi ? -delta : delta);
-        }
+        const T own = FF[(((size_t)slot * 6 + side) * 5 + q) * FACE + rm];
+        const T delta = fine_face(FF, child, nb, side ^ 1, q, m, r) - own;
+        // L changes by -(D_new - D)/dx with D_new - D = +delta (high) / -delta (low)
+        ub[o + q * CELLS_P] += coef * (hi ? -delta : delta);
         __syncthreads();
     }
     }
@@ -1202,7 +1199,7 @@ template <typename T>
 hipError_t launch_reflux(T *L, const T *FF, const WorkList &wl, const DevTables &tb, const InstDev *inst,
                          hipStream_t st) {
     if (wl.grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_reflux<T>, dim3(wl.grid), dim3(TPB), 0, st, L, FF, wl, tb.meta, tb.nbr, inst);
+    hipLaunchKernelGGL(k_reflux<T>, dim3(wl.grid, 5), dim3(TPB), 0, st, L, FF, wl, tb.meta, tb.nbr, tb.child, inst);
     return hipGetLastError();
 }
 
@@ -1356,8 +1353,8 @@ hipError_t launch_reflux_update(int stage, const double *dt, T *U, const T *FF,
                                 const WorkList &wl, const DevTables &tb, const InstDev *inst,
                                 hipStream_t st) {
     if (wl.grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_reflux_update<T>, dim3(wl.grid), dim3(TPB), 0, st, stage, dt, U, FF, wl,
-                       tb.meta, tb.nbr, inst);
+    hipLaunchKernelGGL(k_reflux_update<T>, dim3(wl.grid, 5), dim3(TPB), 0, st, stage, dt, U, FF, wl,
+                       tb.meta, tb.nbr, tb.child, inst);
     return hipGetLastError();
 }
 

@@ -118,8 +118,8 @@ struct HostLists {
     std::vector<int32_t> data;
     int max_level = 0;
     // per level: all blocks, non-leaf blocks, leaves
-    std::vector<int32_t> lvl_off, lvl_cnt, par_off, par_cnt, leaf_off, leaf_cnt, jleaf_off, jleaf_cnt,
-        j26_off, j26_cnt, pfill_off, pfill_cnt, pproj_off, pproj_cnt;
+    std::vector<int32_t> lvl_off, lvl_cnt, par_off, par_cnt, leaf_off, leaf_cnt, j26_off, j26_cnt,
+        pproj_off, pproj_cnt, ffr_off, ffr_cnt, fitem_off, fitem_cnt;
     int32_t all_leaves_off = 0, all_leaves_cnt = 0;      // leaves of every level
     // descriptor table {offset, count} per list, mirrored on the device (graph launches)
     std::vector<int32_t> desc;
@@ -197,20 +197,22 @@ constexpr int DESC_PER_LEVEL = 7;
 constexpr int desc_lvl(int l) { return 5 + DESC_PER_LEVEL * l; }
 constexpr int desc_par(int l) { return 6 + DESC_PER_LEVEL * l; }
 constexpr int desc_leaf(int l) { return 7 + DESC_PER_LEVEL * l; }
-// leaves of level l with at least one face that has no same-level neighbour or lies on a
-// zero-gradient boundary: the only leaves whose halos a fused stage must fill
-constexpr int desc_jleaf(int l) { return 8 + DESC_PER_LEVEL * l; }
 // leaves of level l with at least one of the 26 halo regions lacking a same-level
 // neighbour or on a zero-gradient boundary (filled before the details)
-constexpr int desc_jleaf26(int l) { return 9 + DESC_PER_LEVEL * l; }
-// non-leaf blocks of level l whose halo a stage's predictions read: parents of leaves
-// with a face lacking a same-level neighbour, and parents of such blocks that lack a
-// same-level neighbour in some region themselves
-constexpr int desc_pfill(int l) { return 10 + DESC_PER_LEVEL * l; }
+constexpr int desc_jleaf26(int l) { return 8 + DESC_PER_LEVEL * l; }
 // non-leaf blocks of level l whose interior a stage reads: the stage's prediction
 // sources, their non-leaf same-level neighbours (copied into their halos), non-leaf
 // same-level face neighbours of leaves, and the non-leaf descendants of all of these
-constexpr int desc_pproj(int l) { return 11 + DESC_PER_LEVEL * l; }
+constexpr int desc_pproj(int l) { return 9 + DESC_PER_LEVEL * l; }
+// non-leaf blocks of level l whose restricted face planes the jump correction reads: the
+// non-leaf children beside a coarse leaf (jumps over two levels or more) and their non-leaf
+// descendants; the correction averages leaf children itself
+constexpr int desc_ffr(int l) { return 10 + DESC_PER_LEVEL * l; }
+// a stage's halo fill of level l as items (slot << 5 | region): of the prediction sources
+// (parents of leaves with a face lacking a same-level neighbour, and parents of such blocks
+// that lack a same-level neighbour in some region themselves) the regions in their pmask (0
+// .. 25), of the leaves the faces without a same-level neighbour or on a boundary (26 + side)
+constexpr int desc_fitem(int l) { return 11 + DESC_PER_LEVEL * l; }
 constexpr int N_DESC = 5 + DESC_PER_LEVEL * MAX_LEVELS;
 
 // Halo fill modes, two flags: FACES restricts the fill to the 6 face regions, 3 layers
@@ -220,10 +222,9 @@ constexpr int N_DESC = 5 + DESC_PER_LEVEL * MAX_LEVELS;
 // FILL_RHO_E limits any mode to the density and energy components (the details read
 // nothing else).  FILL_PRESENT (with FILL_FACES) copies only: faces without a same-level
 // neighbour keep their values (the integrated jump halos of local time stepping).
-// FILL_MASKED (with FILL_ALL, for the prediction sources of a stage) fills only the
-// regions in the block's pmask.
+// FILL_ITEMS: the list holds one item per region (desc_fitem) instead of blocks.
 enum FillMode { FILL_ALL = 0, FILL_FACES = 1, FILL_MISSING = 2, FILL_MISSING_FACES = 3, FILL_RHO_E = 4,
-                FILL_PRESENT = 8, FILL_MASKED = 16 };
+                FILL_PRESENT = 8, FILL_ITEMS = 16 };
 
 // --------------------------------------------------------------- kernel launchers ----
 // All launchers enqueue on `st` and return hipGetLastError().
@@ -320,6 +321,17 @@ template <typename T>
 hipError_t launch_reflux_update(int stage, const double *dt, T *U, const T *FF,
                                 const WorkList &leaves, const DevTables &tb,
                                 const InstDev *inst, hipStream_t st);
+// The flux through cell (m, r) of the boundary face `side` of the non-leaf block nb: the area
+// average of its children's four, for component plane offset q * FACE of a face-plane array
+// X[slot][6][5][16][16] (children that are not leaves hold their restricted planes, desc_ffr).
+template <typename T>
+__device__ __forceinline__ T fine_face(const T *__restrict__ X, const int32_t *__restrict__ child, int nb,
+                                       int side, int q, int m, int r) {
+    const int d = side >> 1, hi = side & 1, cm = m >> 3, cr = r >> 3;
+    const int oct = d == 0 ? (cm << 2) | (cr << 1) | hi : d == 1 ? (cm << 2) | (hi << 1) | cr : (hi << 2) | (cm << 1) | cr;
+    const T *c = X + (((size_t)child[(size_t)nb * 8 + oct] * 6 + side) * 5 + q) * FACE + 2 * (m & 7) * NI + 2 * (r & 7);
+    return ((c[0] + c[1]) + (c[NI] + c[NI + 1])) * (T)0.25;
+}
 // Local time stepping (kernels_lts.hip).  F: padded flux divergence [cap][5][24^3];
 // H0: stage-start state of the halo cells of jump faces [cap][6][5][lts_halo_slab()];
 // ACC: time-integrated boundary face fluxes [cap][6][5][16][16] (the layout of FF).

@@ -311,12 +311,8 @@ void Topology::build(std::vector<BlockMeta> &meta, std::vector<int32_t> &child,
     L.par_cnt.assign(maxl + 1, 0);
     L.leaf_off.assign(maxl + 1, 0);
     L.leaf_cnt.assign(maxl + 1, 0);
-    L.jleaf_off.assign(maxl + 1, 0);
-    L.jleaf_cnt.assign(maxl + 1, 0);
     L.j26_off.assign(maxl + 1, 0);
     L.j26_cnt.assign(maxl + 1, 0);
-    L.pfill_off.assign(maxl + 1, 0);
-    L.pfill_cnt.assign(maxl + 1, 0);
     L.pproj_off.assign(maxl + 1, 0);
     L.pproj_cnt.assign(maxl + 1, 0);
     L.par_srestr.assign(maxl + 1, 0);
@@ -369,12 +365,6 @@ void Topology::build(std::vector<BlockMeta> &meta, std::vector<int32_t> &child,
             if (blocks_[s].level == l && pr[s])
                 for (int o = 0; o < 8; ++o) mark_nonleaf(blocks_[s].child[o]);
     const int face_region[6] = {12, 14, 10, 16, 4, 22};
-    auto needs_face_fill = [&](int s) {
-        const BlockMeta &m = meta[s];
-        for (int f = 0; f < 6; ++f)
-            if ((m.zg >> f) & 1 || nbr[(size_t)s * 27 + face_region[f]] < 0) return true;
-        return false;
-    };
     auto needs_region_fill = [&](int s) {
         const BlockMeta &m = meta[s];
         if (m.zg) return true;
@@ -382,7 +372,45 @@ void Topology::build(std::vector<BlockMeta> &meta, std::vector<int32_t> &child,
             if (r != 13 && nbr[(size_t)s * 27 + r] < 0) return true;
         return false;
     };
+    // face planes the jump correction reads beyond leaf children, marked coarse to fine
+    std::vector<char> fr(cap, 0);
+    auto mark_children = [&](int b, int d, int hi) {   // d < 0: all of them
+        for (int o = 0; o < 8; ++o) {
+            const int c = blocks_[b].child[o];
+            if ((d < 0 || ((o >> d) & 1) == hi) && !blocks_[c].leaf) fr[c] = 1;
+        }
+    };
+    for (int s : order) {
+        if (!blocks_[s].leaf) continue;
+        for (int side = 0; side < 6; ++side) {
+            const int nb = nbr[(size_t)s * 27 + face_region[side]];
+            if (nb >= 0 && !blocks_[nb].leaf) mark_children(nb, side >> 1, 1 - (side & 1));
+        }
+    }
+    for (int l = 0; l <= maxl; ++l)
+        for (int s : order)
+            if (blocks_[s].level == l && fr[s]) mark_children(s, -1, 0);
+    L.fitem_off.assign(maxl + 1, 0);
+    L.fitem_cnt.assign(maxl + 1, 0);
+    L.ffr_off.assign(maxl + 1, 0);
+    L.ffr_cnt.assign(maxl + 1, 0);
     for (int l = 0; l <= maxl; ++l) {
+        L.ffr_off[l] = (int32_t)L.data.size();
+        for (int s : order)
+            if (blocks_[s].level == l && fr[s]) L.data.push_back(s);
+        L.ffr_cnt[l] = (int32_t)L.data.size() - L.ffr_off[l];
+        L.fitem_off[l] = (int32_t)L.data.size();
+        for (int s : order) {
+            if (blocks_[s].level != l) continue;
+            if (blocks_[s].leaf) {
+                for (int f = 0; f < 6; ++f)
+                    if ((meta[s].zg >> f) & 1 || nbr[(size_t)s * 27 + face_region[f]] < 0) L.data.push_back(s << 5 | (26 + f));
+            } else if (pf[s]) {
+                for (int i = 0; i < 26; ++i)
+                    if ((meta[s].pmask >> i) & 1) L.data.push_back(s << 5 | i);
+            }
+        }
+        L.fitem_cnt[l] = (int32_t)L.data.size() - L.fitem_off[l];
         L.lvl_off[l] = (int32_t)L.data.size();
         for (int s : order)
             if (blocks_[s].level == l) L.data.push_back(s);
@@ -395,19 +423,11 @@ void Topology::build(std::vector<BlockMeta> &meta, std::vector<int32_t> &child,
         for (int s : order)
             if (blocks_[s].level == l && blocks_[s].leaf) L.data.push_back(s);
         L.leaf_cnt[l] = (int32_t)L.data.size() - L.leaf_off[l];
-        L.jleaf_off[l] = (int32_t)L.data.size();
-        for (int s : order)
-            if (blocks_[s].level == l && blocks_[s].leaf && needs_face_fill(s)) L.data.push_back(s);
-        L.jleaf_cnt[l] = (int32_t)L.data.size() - L.jleaf_off[l];
-        for (int t = L.jleaf_off[l]; t < L.jleaf_off[l] + L.jleaf_cnt[l] && !L.parents_needed; ++t) {
-            const int sl = L.data[t];
-            for (int f = 0; f < 6; ++f)
-                if (!((meta[sl].zg >> f) & 1) && nbr[(size_t)sl * 27 + face_region[f]] < 0) L.parents_needed = true;
-        }
         for (int s : order) {
             if (blocks_[s].level != l || !blocks_[s].leaf || L.parents_needed) continue;
             for (int f = 0; f < 6; ++f) {
                 const int nb = nbr[(size_t)s * 27 + face_region[f]];
+                if (!((meta[s].zg >> f) & 1) && nb < 0) L.parents_needed = true;   // predicted
                 if (nb >= 0 && !blocks_[nb].leaf) L.parents_needed = true;
             }
         }
@@ -415,10 +435,6 @@ void Topology::build(std::vector<BlockMeta> &meta, std::vector<int32_t> &child,
         for (int s : order)
             if (blocks_[s].level == l && blocks_[s].leaf && needs_region_fill(s)) L.data.push_back(s);
         L.j26_cnt[l] = (int32_t)L.data.size() - L.j26_off[l];
-        L.pfill_off[l] = (int32_t)L.data.size();
-        for (int s : order)
-            if (blocks_[s].level == l && !blocks_[s].leaf && pf[s] && meta[s].pmask) L.data.push_back(s);
-        L.pfill_cnt[l] = (int32_t)L.data.size() - L.pfill_off[l];
         L.pproj_off[l] = (int32_t)L.data.size();
         for (int s : order)
             if (blocks_[s].level == l && !blocks_[s].leaf && pr[s]) L.data.push_back(s);
@@ -475,10 +491,10 @@ void Topology::build(std::vector<BlockMeta> &meta, std::vector<int32_t> &child,
         set(desc_lvl(l), L.lvl_off[l], L.lvl_cnt[l]);
         set(desc_par(l), L.par_off[l], L.par_cnt[l]);
         set(desc_leaf(l), L.leaf_off[l], L.leaf_cnt[l]);
-        set(desc_jleaf(l), L.jleaf_off[l], L.jleaf_cnt[l]);
         set(desc_jleaf26(l), L.j26_off[l], L.j26_cnt[l]);
-        set(desc_pfill(l), L.pfill_off[l], L.pfill_cnt[l]);
         set(desc_pproj(l), L.pproj_off[l], L.pproj_cnt[l]);
+        set(desc_ffr(l), L.ffr_off[l], L.ffr_cnt[l]);
+        set(desc_fitem(l), L.fitem_off[l], L.fitem_cnt[l]);
     }
 }
 
