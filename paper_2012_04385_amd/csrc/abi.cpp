@@ -178,7 +178,8 @@ int do_project(mrfv_ctx *ctx, T *U, bool stage_only = false, bool rho_e_only = f
 // reads a parent-derived value).
 // FILL_RHO_E (with FILL_MISSING, before the details) applies to the parents' fill too.
 template <typename T>
-int do_fill(mrfv_ctx *ctx, T *U, int max_level, int mode = FILL_ALL, bool with_parents = true) {
+int do_fill(mrfv_ctx *ctx, T *U, int max_level, int mode = FILL_ALL, bool with_parents = true,
+            int min_level = 0) {
     const int qsel = mode & FILL_RHO_E, m = mode & ~FILL_RHO_E;
     // before the details every non-leaf block gets its full halo; when that is copies only
     // (no prediction reads a coarser level's fill) one launch covers all levels
@@ -187,7 +188,7 @@ int do_fill(mrfv_ctx *ctx, T *U, int max_level, int mode = FILL_ALL, bool with_p
     if (merged)
         HIP_OK(launch_fill_halos<T>(U, wlist(ctx, DESC_PARS, 1024), ctx->tb, (FillMode)(FILL_ALL | qsel),
                                     ctx->stream));
-    for (int l = 0; l <= std::min(max_level, levels_to_cover(ctx)); ++l) {
+    for (int l = min_level; l <= std::min(max_level, levels_to_cover(ctx)); ++l) {
         if (m == FILL_MISSING_FACES) {
             // a stage: the parents' regions its predictions read and the leaves' faces
             HIP_OK(launch_fill_halos<T>(U, wlist(ctx, desc_fitem(l), 4096), ctx->tb, (FillMode)(FILL_ITEMS | qsel), ctx->stream));
@@ -990,15 +991,16 @@ int do_lts_macro(mrfv_ctx *ctx, T *U, T *U0, T *Lb, double *dt, int64_t *cell_up
             const int lo_rhs = st == 0 ? lo_start : lo_end;
             // flux divergence of the leaves being evaluated, from the fused stage kernel (reading
             // same-level neighbours in place, so only boundary halos are filled) into F
-            for (int l = lo_rhs; l <= top; ++l) {
+            // (all levels at once: a level's leaves alone often leave CUs idle)
+            if (lo_rhs <= top) {
                 // the boundary faces (nothing else) when some axis is not periodic
                 if (ctx->bounded)
-                    HIP_OK(launch_fill_halos<T>(U, wlist(ctx, desc_leaf(l)), ctx->tb,
+                    HIP_OK(launch_fill_halos<T>(U, wlist(ctx, desc_from(lo_rhs)), ctx->tb,
                                                 (FillMode)(FILL_MISSING_FACES | FILL_PRESENT), ctx->stream));
                 // (leaves without a non-leaf same-level face neighbour also write the
                 // restriction of their L into the parent's octant of F)
                 HIP_OK(launch_rhs_update<T>(flux_kernel(ctx), ctx->rhs_variant, RHS_TO_FIELD, dt, U, F, U0,
-                                            wlist(ctx, desc_leaf(l), 1 << 30), ctx->tb, ctx->d_inst, FF,
+                                            wlist(ctx, desc_from(lo_rhs), 1 << 30), ctx->tb, ctx->d_inst, FF,
                                             ctx->d_err, 1, nullptr, false, ctx->stream));
             }
             // averaged into the parents (the octants the fused kernel wrote are skipped: every
@@ -1008,17 +1010,18 @@ int do_lts_macro(mrfv_ctx *ctx, T *U, T *U0, T *Lb, double *dt, int64_t *cell_up
                 if (L.par_srestr[p]) continue;   // every child wrote its octant
                 HIP_OK(launch_project<T>(F, wlist(ctx, desc_par(p)), ctx->tb, ctx->stream, 31, true));
             }
-            CALL(do_fill<T>(ctx, F, 1 << 20, FILL_MISSING_FACES, true));
+            // (coarser levels' regions keep their values: what they are copied and predicted
+            // from, levels l and l - 1, changed down to the parents of level lo_rhs only)
+            CALL(do_fill<T>(ctx, F, 1 << 20, FILL_MISSING_FACES, true, std::max(lo_rhs, 1) - 1));
             // algo:Integration of the levels that end a step at r
-            for (int l = lo_end; l <= top; ++l)
-                HIP_OK(launch_lts_update<T>(st, dt, U, U0, H0, F, FF, ACC, wlist(ctx, desc_leaf(l)), ctx->tb,
+            if (lo_end <= top)
+                HIP_OK(launch_lts_update<T>(st, dt, U, U0, H0, F, FF, ACC, wlist(ctx, desc_from(lo_end)), ctx->tb,
                                             ctx->d_inst, ctx->d_err, ctx->stream));
-            if (st == 2 && ctx->has_jumps) {
+            if (st == 2 && ctx->has_jumps && lo_end <= top) {
                 for (int p = top - 1; p >= lo_end; --p)
                     HIP_OK(launch_ff_restrict<T>(ACC, wlist(ctx, desc_ffr(p)), ctx->tb, ctx->stream));
-                for (int l = lo_end; l <= top; ++l)
-                    HIP_OK(launch_lts_adjust<T>(U, ACC, wlist(ctx, desc_leaf(l)), ctx->tb, ctx->d_inst,
-                                                ctx->stream));
+                HIP_OK(launch_lts_adjust<T>(U, ACC, wlist(ctx, desc_from(lo_end)), ctx->tb, ctx->d_inst,
+                                            ctx->stream));
             }
             if (st == 2)
                 HIP_OK(launch_lts_zero<T>(ACC, wlist(ctx, DESC_LEAVES), ctx->tb, lo_end, ctx->stream));
@@ -1089,8 +1092,8 @@ int mrfv_create(mrfv_ctx **out, const mrfv_config *cfg, const mrfv_instance *ins
         return bail(MRFV_EHIP);
     }
     const size_t cap = cfg->slot_capacity, es = elem_size(ctx);
-    // lists of blocks (at most 9 per block) and fill items (26 per parent, 6 per leaf)
-    ctx->lists_cap = 2 * cfg->n_instances + 19 * cfg->slot_capacity + 64;
+    // lists of blocks (at most 10 per block) and fill items (26 per parent, 6 per leaf)
+    ctx->lists_cap = 2 * cfg->n_instances + 20 * cfg->slot_capacity + 64;
     ctx->prim_batch = 128;
     ctx->lvl_bound.assign(MAX_LEVELS, 0);
     for (int i = 0; i < cfg->n_instances; ++i) {

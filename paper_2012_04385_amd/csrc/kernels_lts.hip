@@ -69,10 +69,21 @@ __device__ __forceinline__ bool lts_physical(const T u[5], const InstDev &P) {
     return u[0] > (T)0 && p + B > (T)0 && isfinite(u[4]) && isfinite(u[1] + u[2] + u[3]);
 }
 
+// Four consecutive cells of a row: interior rows start 16-byte aligned in the padded arrays
+// (index 4 of rows of 24) and in U0 when the arrays' bases are, so the interior update moves
+// them with 16-byte accesses.
+template <typename T>
+struct alignas(16) Quad {
+    T v[4];
+};
+
 // blockIdx.y = part: interior z-planes [PLANES * part, PLANES * (part + 1)) and face pieces
 // [PIECES * part, PIECES * (part + 1)) of 24: side * 3 + halo layer for pieces below 18,
 // then the face-flux sums of one side.
-template <typename T>
+// VEC: U, U0 and F are 16-byte aligned (the host checks); a thread then owns four consecutive
+// cells of one row, one quad per array and component, instead of one cell in each of four
+// planes.
+template <typename T, bool VEC>
 __global__ __launch_bounds__(TPB) void k_lts_update(int stage, const double *__restrict__ dt,
                                                     T *U, T *U0, T *H0, const T *__restrict__ F,
                                                     const T *__restrict__ FF, T *ACC, WorkList wl,
@@ -90,7 +101,38 @@ __global__ __launch_bounds__(TPB) void k_lts_update(int stage, const double *__r
         const T a = lts_stage_coef<T>(stage);
         T *ub = U + (size_t)slot * 5 * CELLS_P;
         const T *fb = F + (size_t)slot * 5 * CELLS_P;
-        {
+        if constexpr (VEC) {
+            // interior: every load before the first store (U is read and written through
+            // the same pointer)
+            const int e = part * TPB + tid;   // quad: z, y, x / 4
+            const int c = 4 * e, o = ((e / 64 + HW) * NP + (e / 4) % NI + HW) * NP + (e % 4) * 4 + HW;
+            T *u0b = U0 + (size_t)slot * 5 * CELLS_I;
+            Quad<T> us[5], fl[5], u0[5];
+#pragma unroll
+            for (int q = 0; q < 5; ++q) {
+                us[q] = *(const Quad<T> *)(ub + o + q * CELLS_P);
+                fl[q] = *(const Quad<T> *)(fb + o + q * CELLS_P);
+                if (stage == 0) u0[q] = us[q];
+                else u0[q] = *(const Quad<T> *)(u0b + q * CELLS_I + c);
+            }
+            bool ok = true;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                T un[5];
+#pragma unroll
+                for (int q = 0; q < 5; ++q)
+                    un[q] = u0[q].v[k] + a * ((us[q].v[k] - u0[q].v[k]) + (T)dtl * fl[q].v[k]);
+                ok = ok && lts_physical(un, P);
+#pragma unroll
+                for (int q = 0; q < 5; ++q) us[q].v[k] = un[q];
+            }
+#pragma unroll
+            for (int q = 0; q < 5; ++q) {
+                if (stage == 0) *(Quad<T> *)(u0b + q * CELLS_I + c) = u0[q];
+                *(Quad<T> *)(ub + o + q * CELLS_P) = us[q];
+            }
+            if (!ok) atomicOr(err, 1);
+        } else {
             // interior: every load of the four planes before the first store (U is read
             // and written through the same pointer, so the compiler keeps program order)
             T *u0b = U0 + (size_t)slot * 5 * CELLS_I;
@@ -216,8 +258,13 @@ hipError_t launch_lts_update(int stage, const double *dt, T *U, T *U0, T *H0, co
                              const T *FF, T *ACC, const WorkList &wl, const DevTables &tb,
                              const InstDev *inst, int32_t *err, hipStream_t st) {
     if (wl.grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_lts_update<T>, dim3(wl.grid, PARTS), dim3(TPB), 0, st, stage, dt, U,
-                       U0, H0, F, FF, ACC, wl, tb.meta, tb.nbr, inst, err);
+    static_assert(PARTS * TPB * 4 == CELLS_I, "a quad per thread");
+    if ((((uintptr_t)U | (uintptr_t)U0 | (uintptr_t)F) & 15) == 0)
+        hipLaunchKernelGGL((k_lts_update<T, true>), dim3(wl.grid, PARTS), dim3(TPB), 0, st, stage, dt, U,
+                           U0, H0, F, FF, ACC, wl, tb.meta, tb.nbr, inst, err);
+    else
+        hipLaunchKernelGGL((k_lts_update<T, false>), dim3(wl.grid, PARTS), dim3(TPB), 0, st, stage, dt, U,
+                           U0, H0, F, FF, ACC, wl, tb.meta, tb.nbr, inst, err);
     return hipGetLastError();
 }
 

@@ -119,7 +119,8 @@ struct HostLists {
     int max_level = 0;
     // per level: all blocks, non-leaf blocks, leaves
     std::vector<int32_t> lvl_off, lvl_cnt, par_off, par_cnt, leaf_off, leaf_cnt, j26_off, j26_cnt,
-        pproj_off, pproj_cnt, ffr_off, ffr_cnt, fitem_off, fitem_cnt;
+        pproj_off, pproj_cnt, ffr_off, ffr_cnt, fitem_off, fitem_cnt,
+        from_off, from_cnt;
     int32_t all_leaves_off = 0, all_leaves_cnt = 0;      // leaves of every level
     // descriptor table {offset, count} per list, mirrored on the device (graph launches)
     std::vector<int32_t> desc;
@@ -193,7 +194,7 @@ constexpr int MAX_LEVELS = 13;
 // changes their boundary cells after the fused stage)
 // DESC_PARS: every non-leaf block, all levels
 constexpr int DESC_LEAVES = 0, DESC_ALL = 1, DESC_FINE = 2, DESC_JCORR = 3, DESC_PARS = 4;
-constexpr int DESC_PER_LEVEL = 7;
+constexpr int DESC_PER_LEVEL = 8;
 constexpr int desc_lvl(int l) { return 5 + DESC_PER_LEVEL * l; }
 constexpr int desc_par(int l) { return 6 + DESC_PER_LEVEL * l; }
 constexpr int desc_leaf(int l) { return 7 + DESC_PER_LEVEL * l; }
@@ -213,6 +214,8 @@ constexpr int desc_ffr(int l) { return 10 + DESC_PER_LEVEL * l; }
 // that lack a same-level neighbour in some region themselves) the regions in their pmask (0
 // .. 25), of the leaves the faces without a same-level neighbour or on a boundary (26 + side)
 constexpr int desc_fitem(int l) { return 11 + DESC_PER_LEVEL * l; }
+// leaves of level l and finer (local time stepping evaluates and integrates such ranges)
+constexpr int desc_from(int l) { return 12 + DESC_PER_LEVEL * l; }
 constexpr int N_DESC = 5 + DESC_PER_LEVEL * MAX_LEVELS;
 
 // Halo fill modes, two flags: FACES restricts the fill to the 6 face regions, 3 layers

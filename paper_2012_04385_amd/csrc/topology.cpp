@@ -390,6 +390,8 @@ void Topology::build(std::vector<BlockMeta> &meta, std::vector<int32_t> &child,
     for (int l = 0; l <= maxl; ++l)
         for (int s : order)
             if (blocks_[s].level == l && fr[s]) mark_children(s, -1, 0);
+    L.from_off.assign(maxl + 1, 0);
+    L.from_cnt.assign(maxl + 1, 0);
     L.fitem_off.assign(maxl + 1, 0);
     L.fitem_cnt.assign(maxl + 1, 0);
     L.ffr_off.assign(maxl + 1, 0);
@@ -442,6 +444,12 @@ void Topology::build(std::vector<BlockMeta> &meta, std::vector<int32_t> &child,
         L.par_srestr[l] = all_srestr(L.par_off[l], L.par_cnt[l]);
         L.pproj_srestr[l] = all_srestr(L.pproj_off[l], L.pproj_cnt[l]);
     }
+    for (int l = 0; l <= maxl; ++l) {
+        L.from_off[l] = (int32_t)L.data.size();
+        for (int s : order)
+            if (blocks_[s].level == l && blocks_[s].leaf) L.data.push_back(s);
+    }
+    for (int l = 0; l <= maxl; ++l) L.from_cnt[l] = (int32_t)L.data.size() - L.from_off[l];
     L.all_leaves_off = (int32_t)L.data.size();
     for (int i = 0; i < n_inst; ++i) {
         L.data[i] = (int32_t)L.data.size();
@@ -495,6 +503,7 @@ void Topology::build(std::vector<BlockMeta> &meta, std::vector<int32_t> &child,
         set(desc_pproj(l), L.pproj_off[l], L.pproj_cnt[l]);
         set(desc_ffr(l), L.ffr_off[l], L.ffr_cnt[l]);
         set(desc_fitem(l), L.fitem_off[l], L.fitem_cnt[l]);
+        set(desc_from(l), L.from_off[l], L.from_cnt[l]);
     }
 }
 
