@@ -26,13 +26,14 @@ namespace {
 constexpr int TPB = 256;                  // one thread per cell of a z-plane
 constexpr int SLAB = 3 * FACE;            // halo cells of one face that the flux reads
 // The stage update runs four workgroups per leaf, each over four interior z-planes (its
-// loads issued together) and six of the leaf's 24 face pieces (18 halo layers, 6 face-flux
-// sums), most of which are skipped: one workgroup per plane and piece took 41 % longer in
-// FP32 (27 % in FP64), most of it in starting workgroups that had little or nothing to do.
+// loads issued together) and three of the leaf's 12 face pieces (halos of a side, face-flux
+// sums of a side), most of which are skipped: one workgroup per plane and piece took 41 %
+// longer in FP32 (27 % in FP64), most of it in starting workgroups that had little or nothing
+// to do.
 constexpr int PLANES = 4;
 constexpr int PARTS = NI / PLANES;
-constexpr int PIECES = (6 * 3 + 6) / PARTS;
-static_assert(NI % PLANES == 0 && (6 * 3 + 6) % PARTS == 0, "parts must tile the leaf");
+constexpr int PIECES = 12;                // the halo of each side (three layers), its sums
+static_assert(NI % PLANES == 0, "parts must tile the leaf");
 
 __device__ __forceinline__ int pidx(int q, int k, int j, int i) {
     return ((q * NP + k) * NP + j) * NP + i;
@@ -77,9 +78,8 @@ struct alignas(16) Quad {
     T v[4];
 };
 
-// blockIdx.y = part: interior z-planes [PLANES * part, PLANES * (part + 1)) and face pieces
-// [PIECES * part, PIECES * (part + 1)) of 24: side * 3 + halo layer for pieces below 18,
-// then the face-flux sums of one side.
+// blockIdx.y = part: interior z-planes [PLANES * part, PLANES * (part + 1)) and every PARTS-th
+// of the 12 face pieces: the three halo layers of a side, then the face-flux sums of a side.
 // VEC: U, U0 and F are 16-byte aligned (the host checks); a thread then owns four consecutive
 // cells of one row, one quad per array and component, instead of one cell in each of four
 // planes.
@@ -163,31 +163,35 @@ __global__ __launch_bounds__(TPB) void k_lts_update(int stage, const double *__r
             }
             if (!ok) atomicOr(err, 1);
         }
-        for (int f = part * PIECES; f < (part + 1) * PIECES; ++f) {
-            if (f < 18) {
-                const int side = f / 3, h = f % 3;
-                if (nbr[(size_t)slot * 27 + face_region(side)] != -1) continue;   // not a jump face
+#pragma unroll 1
+        for (int f = part; f < PIECES; f += PARTS) {
+            const int side = f % 6, nbs = nbr[(size_t)slot * 27 + face_region(side)];
+            if (f < 6) {
+                if (nbs != -1) continue;   // not a jump face
                 const int d = side >> 1, hi = side & 1;
-                const int p = hi ? HW + NI + h : HW - 3 + h;
-                T *h0 = H0 + ((size_t)slot * 6 + side) * 5 * SLAB + h * FACE + tid;
+                T *h0 = H0 + ((size_t)slot * 6 + side) * 5 * SLAB + tid;
+                T us[3][5], u0[3][5], fl[3][5];   // all loads of the three layers together
+                int n[3];
 #pragma unroll
-                for (int q = 0; q < 5; ++q) {
-                    const int n = plane_cell(q, d, p, tid >> 4, tid & 15);
-                    const T us = ub[n];
-                    T u0;
-                    if (stage == 0) {
-                        u0 = us;
-                        h0[q * SLAB] = us;
-                    } else {
-                        u0 = h0[q * SLAB];
+                for (int h = 0; h < 3; ++h) {
+                    n[h] = plane_cell(0, d, hi ? HW + NI + h : HW - 3 + h, tid >> 4, tid & 15);
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) {
+                        us[h][q] = ub[n[h] + q * CELLS_P];
+                        fl[h][q] = fb[n[h] + q * CELLS_P];
+                        u0[h][q] = stage == 0 ? us[h][q] : h0[q * SLAB + h * FACE];
                     }
-                    ub[n] = u0 + a * ((us - u0) + (T)dtl * fb[n]);
                 }
+#pragma unroll
+                for (int h = 0; h < 3; ++h)
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) {
+                        if (stage == 0) h0[q * SLAB + h * FACE] = us[h][q];
+                        ub[n[h] + q * CELLS_P] = u0[h][q] + a * ((us[h][q] - u0[h][q]) + (T)dtl * fl[h][q]);
+                    }
             } else {
                 // only faces that a coarse cell adjustment reads: jump faces (the fine side)
                 // and faces whose same-level neighbour is refined (the coarse side)
-                const int side = f - 18;
-                const int nbs = nbr[(size_t)slot * 27 + face_region(side)];
                 if (!(nbs == -1 || (nbs >= 0 && !meta[nbs].leaf))) continue;
                 const double bw = stage == 2 ? 2.0 / 3.0 : 1.0 / 6.0;
                 const T w = (T)(bw * dtl);
