@@ -889,57 +889,70 @@ __global__ __launch_bounds__(CTPB) void k_cfl_inst(WorkList leaves,
     }
 }
 
-// Per-block FP64 sums of the 5 conserved quantities over the interior (fixed tree).
+// Sums of five values over a workgroup of TPB_ threads in a fixed order: over each wavefront,
+// then over the wavefronts; the result is thread 0's.
+template <int TPB_>
+__device__ __forceinline__ void sum5(double (&s)[5], double (*red)[5]) {
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        for (int off = 32; off > 0; off >>= 1) s[q] += __shfl_xor(s[q], off);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][q] = s[q];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            s[q] = red[0][q];
+            for (int w = 1; w < TPB_ / 64; ++w) s[q] += red[w][q];
+        }
+    __syncthreads();
+}
+
+// Per-block FP64 sums of the 5 conserved quantities over the interior (fixed order); the five
+// sums share their loads' latency and two barriers (one tree of barriers per quantity took 30
+// us for 792 leaves, this 17).
 template <typename T>
 __global__ __launch_bounds__(TPB) void k_sum_block(const T *__restrict__ U, WorkList wl,
                                                    double *__restrict__ bsum) {
-    __shared__ double red[TPB];
+    __shared__ double red[TPB / 64][5];
     const int nb = wl.count();
     for (int b = blockIdx.x; b < nb; b += gridDim.x) {
     const int slot = wl.at(b);
     const T *u = U + (size_t)slot * 5 * CELLS_P;
-    for (int q = 0; q < 5; ++q) {
-        double s = 0.0;
-        for (int c = threadIdx.x; c < CELLS_I; c += TPB)
-            s += (double)u[pidx(q, HW + c / FACE, HW + (c / NI) % NI, HW + c % NI)];
-        red[threadIdx.x] = s;
-        __syncthreads();
-        for (int w = TPB / 2; w > 0; w >>= 1) {
-            if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) bsum[(size_t)slot * 5 + q] = red[0];
-        __syncthreads();
-    }
+    double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int c = threadIdx.x; c < CELLS_I; c += TPB)
+#pragma unroll
+        for (int q = 0; q < 5; ++q) s[q] += (double)u[pidx(q, HW + c / FACE, HW + (c / NI) % NI, HW + c % NI)];
+    sum5<TPB>(s, red);
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int q = 0; q < 5; ++q) bsum[(size_t)slot * 5 + q] = s[q];
     }
 }
 
-__global__ __launch_bounds__(TPB) void k_sum_inst(const int32_t *__restrict__ list,
-                                                  const int32_t *__restrict__ off,
-                                                  const int32_t *__restrict__ cnt,
-                                                  const BlockMeta *__restrict__ meta,
-                                                  const InstDev *__restrict__ inst,
-                                                  const double *__restrict__ bsum,
-                                                  double *__restrict__ tot) {
-    __shared__ double red[TPB];
+constexpr int STPB = 1024;   // threads of the per-instance sums
+__global__ __launch_bounds__(STPB) void k_sum_inst(const int32_t *__restrict__ list,
+                                                   const int32_t *__restrict__ off,
+                                                   const int32_t *__restrict__ cnt,
+                                                   const BlockMeta *__restrict__ meta,
+                                                   const InstDev *__restrict__ inst,
+                                                   const double *__restrict__ bsum,
+                                                   double *__restrict__ tot) {
+    __shared__ double red[STPB / 64][5];
     const int ins = blockIdx.x;
-    const InstDev P = inst[ins];
-    for (int q = 0; q < 5; ++q) {
-        double s = 0.0;
-        for (int t = threadIdx.x; t < cnt[ins]; t += TPB) {
-            const int slot = list[off[ins] + t];
-            const double dx = ldexp(P.dx0, -meta[slot].level);
-            s += bsum[(size_t)slot * 5 + q] * (dx * dx * dx);
-        }
-        red[threadIdx.x] = s;
-        __syncthreads();
-        for (int w = TPB / 2; w > 0; w >>= 1) {
-            if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) tot[ins * 5 + q] = red[0];
-        __syncthreads();
+    const double dx0 = inst[ins].dx0;
+    double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int t = threadIdx.x; t < cnt[ins]; t += STPB) {
+        const int slot = list[off[ins] + t];
+        const double dx = ldexp(dx0, -meta[slot].level);
+#pragma unroll
+        for (int q = 0; q < 5; ++q) s[q] += bsum[(size_t)slot * 5 + q] * (dx * dx * dx);
     }
+    sum5<STPB>(s, red);
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int q = 0; q < 5; ++q) tot[ins * 5 + q] = s[q];
 }
 
 inline dim3 grid2(int n, int y) { return dim3((unsigned)n, (unsigned)y, 1); }
@@ -1050,7 +1063,7 @@ hipError_t launch_totals(const T *U, const WorkList &leaves, const DevTables &tb
                          hipStream_t st) {
     if (leaves.grid <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_sum_block<T>, dim3(leaves.grid), dim3(TPB), 0, st, U, leaves, blocksum);
-    hipLaunchKernelGGL(k_sum_inst, dim3(n_inst), dim3(TPB), 0, st, tb.lists, tb.lists,
+    hipLaunchKernelGGL(k_sum_inst, dim3(n_inst), dim3(STPB), 0, st, tb.lists, tb.lists,
                        tb.lists + n_inst, tb.meta, inst, blocksum, tot);
     return hipGetLastError();
 }
