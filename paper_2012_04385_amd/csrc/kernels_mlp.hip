@@ -27,47 +27,61 @@ __device__ __forceinline__ uint16_t to_bf16(float x) {
     return (uint16_t)(u >> 16);
 }
 
-// Features of every listed leaf, one workgroup per block: 4 threads per sub-cube, each
-// summing one 4x4 layer of it; rows of X follow the list order.
+// Features of every listed leaf, one workgroup per block, a thread per (x, y) column: rho, the
+// three momenta and E are read once, coalesced along x, and the density's neighbours come from
+// LDS (16^3 floats).  Reading them again from memory, four lanes per sub-cube along z, took
+// 119 us for 792 leaves (each load touched 16 rows); this form takes 30 us.  A sub-cube's sums
+// are formed in the order of that form: each 4 x 4 layer of it row by row by one lane, then
+// the layers pairwise.
 template <typename T>
 __global__ __launch_bounds__(TPB) void k_features(const T *__restrict__ U, WorkList wl,
                                                   const BlockMeta *__restrict__ meta,
                                                   const InstDev *__restrict__ inst,
                                                   float *__restrict__ X) {
+    // per cell: density, pressure, then |grad rho|; a row of 16 cells padded by one word so
+    // that the lanes of a reduction (sub-cubes 4 cells apart) spread over the banks
+    constexpr int RS = NI + 1, PS = NI * RS;
+    __shared__ float R[NI * PS], Pr[NI * PS], Gr[NI * PS];
     const int nb = wl.count();
+    const int tid = threadIdx.x;
     for (int b = blockIdx.x; b < nb; b += gridDim.x) {
         const int slot = wl.at(b);
         const BlockMeta m = meta[slot];
         const InstDev P = inst[m.inst];
         const T *u = U + (size_t)slot * 5 * CELLS_P;
-        const int s = threadIdx.x >> 2, part = threadIdx.x & 3;
-        const int sx = s & 3, sy = (s >> 2) & 3, sz = s >> 4;
-        const int k = 4 * sz + part;
         const float g = (float)P.gamma, Bp = (float)P.B;
-        auto rho = [&](int kk, int jj, int ii) {
-            return (float)u[((HW + kk) * NP + HW + jj) * NP + HW + ii];
+        const int x = tid & 15, y = tid >> 4;
+#pragma unroll 4
+        for (int k = 0; k < NI; ++k) {
+            const int o = ((HW + k) * NP + HW + y) * NP + HW + x;
+            const float r = (float)u[o];
+            const float m1 = (float)u[o + CELLS_P], m2 = (float)u[o + 2 * CELLS_P],
+                        m3 = (float)u[o + 3 * CELLS_P], E = (float)u[o + 4 * CELLS_P];
+            R[k * PS + y * RS + x] = r;
+            Pr[k * PS + y * RS + x] = (g - 1.f) * (E - 0.5f * (m1 * m1 + m2 * m2 + m3 * m3) / r) - g * Bp;
+        }
+        __syncthreads();
+        // central differences inside the block, one-sided at its faces
+        auto diff = [&](int at, int i, int st) {
+            return i == 0 ? R[at + st] - R[at]
+                          : (i == NI - 1 ? R[at] - R[at - st] : 0.5f * (R[at + st] - R[at - st]));
         };
+#pragma unroll 4
+        for (int k = 0; k < NI; ++k) {
+            const int at = k * PS + y * RS + x;
+            const float gx = diff(at, x, 1), gy = diff(at, y, RS), gz = diff(at, k, PS);
+            Gr[at] = sqrtf(gx * gx + gy * gy + gz * gz);
+        }
+        __syncthreads();
+        const int s = tid >> 2, part = tid & 3;
+        const int sx = s & 3, sy = (s >> 2) & 3, sz = s >> 4;
         float sr = 0.f, sg = 0.f, sp = 0.f;
-        for (int j = 4 * sy; j < 4 * sy + 4; ++j)
-            for (int i = 4 * sx; i < 4 * sx + 4; ++i) {
-                const int o = ((HW + k) * NP + HW + j) * NP + HW + i;
-                const float r = (float)u[o];
-                const float m1 = (float)u[o + CELLS_P], m2 = (float)u[o + 2 * CELLS_P],
-                            m3 = (float)u[o + 3 * CELLS_P], E = (float)u[o + 4 * CELLS_P];
-                const float p = (g - 1.f) * (E - 0.5f * (m1 * m1 + m2 * m2 + m3 * m3) / r) - g * Bp;
-                // central differences inside the block, one-sided at its faces
-                const float gx = i == 0 ? rho(k, j, 1) - rho(k, j, 0)
-                               : (i == NI - 1 ? rho(k, j, NI - 1) - rho(k, j, NI - 2)
-                                              : 0.5f * (rho(k, j, i + 1) - rho(k, j, i - 1)));
-                const float gy = j == 0 ? rho(k, 1, i) - rho(k, 0, i)
-                               : (j == NI - 1 ? rho(k, NI - 1, i) - rho(k, NI - 2, i)
-                                              : 0.5f * (rho(k, j + 1, i) - rho(k, j - 1, i)));
-                const float gz = k == 0 ? rho(1, j, i) - rho(0, j, i)
-                               : (k == NI - 1 ? rho(NI - 1, j, i) - rho(NI - 2, j, i)
-                                              : 0.5f * (rho(k + 1, j, i) - rho(k - 1, j, i)));
-                sr += r;
-                sg += sqrtf(gx * gx + gy * gy + gz * gz);
-                sp += p;
+        for (int j = 0; j < 4; ++j)
+            for (int i = 0; i < 4; ++i) {
+                const int at = (4 * sz + part) * PS + (4 * sy + j) * RS + 4 * sx + i;
+                sr += R[at];
+                sg += Gr[at];
+                sp += Pr[at];
             }
         // the four parts of a sub-cube are consecutive lanes
         sr += __shfl_xor(sr, 1);
@@ -79,10 +93,10 @@ __global__ __launch_bounds__(TPB) void k_features(const T *__restrict__ U, WorkL
         if (part == 0) {
             const float eps_l = (float)ldexp(P.eps, -3 * (P.lmax - m.level));
             const float s_rho = (float)P.scale_rho, s_p = (float)(P.scale_E * (P.gamma - 1.0));
-            float *x = X + (size_t)b * 192 + 3 * s;
-            x[0] = sr * (1.f / 64.f) / s_rho - 1.f;
-            x[1] = logf(1.f + sg * (1.f / 64.f) / (s_rho * eps_l));
-            x[2] = sp * (1.f / 64.f) / s_p - 1.f;
+            float *x_ = X + (size_t)b * 192 + 3 * s;
+            x_[0] = sr * (1.f / 64.f) / s_rho - 1.f;
+            x_[1] = logf(1.f + sg * (1.f / 64.f) / (s_rho * eps_l));
+            x_[2] = sp * (1.f / 64.f) / s_p - 1.f;
         }
         __syncthreads();
     }
@@ -120,6 +134,45 @@ __global__ __launch_bounds__(TPB) void k_gemm_bf16(const uint16_t *__restrict__ 
         float *c = C + (size_t)(tm * 16 + 4 * kq + e) * ldc + tn * 16 + i;
         *c = accumulate ? *c + acc[e] : acc[e];
     }
+}
+
+// The same product for the weight gradients, whose sum runs over the samples (K up to
+// max_rows) and whose tiles are few (4 to 48): one workgroup per tile, each of its 16
+// wavefronts sums every 16th block of 16 samples, and the partial tiles are added through LDS
+// in wavefront order.  One wavefront per tile walked 4096 samples in 256 dependent steps
+// (three products 240 us at 4096 samples); this takes 33.
+constexpr int KWAVES = 16;
+__global__ __launch_bounds__(64 * KWAVES) void k_gemm_bf16_long(const uint16_t *__restrict__ A, int sam, int sak,
+                                                                const uint16_t *__restrict__ B, int sbk, int sbn,
+                                                                float *__restrict__ C, int ldc, int Nn, int K) {
+    __shared__ f32x4 part[KWAVES][64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int tiles_n = Nn / 16, tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
+    const int i = lane & 15, kq = lane >> 4;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    const uint16_t *Arow = A + (size_t)(tm * 16 + i) * sam;
+    const uint16_t *Bcol = B + (size_t)(tn * 16 + i) * sbn;
+#pragma unroll 4
+    for (int k0 = 16 * wave; k0 < K; k0 += 16 * KWAVES) {
+        bf16x4 a, b;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int k = k0 + 4 * kq + e;
+            a[e] = (short)Arow[(size_t)k * sak];
+            b[e] = (short)Bcol[(size_t)k * sbk];
+        }
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
+    }
+    part[wave][lane] = acc;
+    __syncthreads();
+    if (wave) return;
+    for (int w = 1; w < KWAVES; ++w) {
+        const f32x4 p = part[w][lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += p[e];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) C[(size_t)(tm * 16 + 4 * kq + e) * ldc + tn * 16 + i] = acc[e];
 }
 
 // out[r][c] = bf16(in[r*ldi + c]) for r < rows, c < cols; zero padding up to
@@ -235,6 +288,13 @@ hipError_t launch_gemm_bf16(const uint16_t *A, int sam, int sak, const uint16_t 
                             float *C, int ldc, int M, int Nn, int K, int accumulate, hipStream_t st) {
     const int tiles = (M / 16) * (Nn / 16);
     if (tiles <= 0) return hipSuccess;
+    // the weight gradients: long sums over few tiles (fewer tiles than CUs, and each wavefront
+    // has at least one block of samples)
+    if (!accumulate && tiles < 256 && K >= 16 * KWAVES) {
+        hipLaunchKernelGGL(k_gemm_bf16_long, dim3(tiles), dim3(64 * KWAVES), 0, st, A, sam, sak, B, sbk, sbn, C,
+                           ldc, Nn, K);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_gemm_bf16, dim3((tiles + 3) / 4), dim3(TPB), 0, st, A, sam, sak, B, sbk, sbn, C,
                        ldc, M, Nn, K, accumulate);
     return hipGetLastError();
