@@ -327,7 +327,7 @@ int do_details_flags(mrfv_ctx *ctx, const T *U, int8_t *flags, double *det,
                      int8_t *flags_host = nullptr, int32_t *err_host = nullptr,
                      int32_t *gate = nullptr) {
     HIP_OK(launch_details<T>(U, wlist(ctx, DESC_FINE), ctx->tb, ctx->d_inst, ctx->d_det4, ctx->d_recheck, ctx->stream));
-    HIP_OK(launch_flags(wlist(ctx, DESC_ALL), ctx->tb, ctx->d_inst, ctx->d_det4, det, flags, flags_host,
+    HIP_OK(launch_flags(wlist(ctx, DESC_ALL, 1 << 30), ctx->tb, ctx->d_inst, ctx->d_det4, det, flags, flags_host,
                         ctx->d_err, err_host, gate, ctx->cfg.slot_capacity, ctx->stream));
     return MRFV_OK;
 }

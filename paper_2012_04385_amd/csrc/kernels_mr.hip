@@ -14,6 +14,7 @@
 // c0 = -22/128, c1 = 3/128 (Q_x = D_x u, Q_xy = D_x D_y u, Q_xyz = D_x D_y D_z u), so the
 // child value is (1 + s_z D_z)(1 + s_y D_y)(1 + s_x D_x) u, s = +1 for the lower child.
 // Written in difference form it reproduces a uniform field exactly.
+#include <algorithm>
 #include <mutex>
 
 #include "mrfv_internal.h"
@@ -170,12 +171,21 @@ __device__ __forceinline__ int parent_of(int c, int o) { return o * (NI / 2) + (
 // regions), y pass (16 x 16 x 6 for z-normal regions, else 16 x 4 x 12).
 constexpr int PR_A = 6 * 12 * 12, PR_X = 16 * 12 * 6, PR_Y = 16 * 16 * 6;
 
+// Four consecutive cells of a padded row from an index divisible by four: every halo region
+// starts and ends at such an index along x, as does the interior, so rows are copied in
+// quads (16-byte accesses) where the array's base is 16-byte aligned.
+template <typename T>
+struct alignas(16) Quad {
+    T v[4];
+};
+
 // EXT: the context has symmetry or fixed-value sides; without them the mirror and
 // fixed-value code is compiled out (the periodic / zero-gradient fill pays nothing for it).
+// blockIdx.z: components blockIdx.z, blockIdx.z + gridDim.z, ...; vec: U is 16-byte aligned.
 template <typename T, bool EXT>
 __global__ __launch_bounds__(TPB) void k_fill_halos(T *__restrict__ U, WorkList wl,
                                                     const BlockMeta *__restrict__ meta,
-                                                    const int32_t *__restrict__ nbr, int mode,
+                                                    const int32_t *__restrict__ nbr, int mode, int vec,
                                                     const T *__restrict__ bcfix) {
     __shared__ T A[PR_A];
     __shared__ T X[PR_X];
@@ -218,7 +228,7 @@ __global__ __launch_bounds__(TPB) void k_fill_halos(T *__restrict__ U, WorkList 
                     const int layer = fhi ? cf - (HW + NI) : HW - 1 - cf;
     #pragma unroll
                     for (int q = 0; q < 5; ++q) {
-                        if (re && q != 0 && q != 4) continue;
+                        if ((re && q != 0 && q != 4) || (re ? q / 4 : q) % (int)gridDim.z != (int)blockIdx.z) continue;
                         const bool flip = q >= 1 && q <= 3 && ((flipbits >> (q - 1)) & 1);
                         const T v = fv[layer * 5 + q];
                         dst[pidx(q, ck, cj, ci)] = flip ? -v : v;
@@ -235,7 +245,9 @@ __global__ __launch_bounds__(TPB) void k_fill_halos(T *__restrict__ U, WorkList 
             const int ncell = g.n[0] * g.n[1] * g.n[2];
             const Div dc(ncell), d0(g.n[0]), d1(g.n[1]);
             const bool re = (mode & FILL_RHO_E) != 0;
-            const int nq = re ? 2 : 5;
+            // this workgroup's components: z0, z0 + gridDim.z, ...
+            const int zn = gridDim.z, z0 = blockIdx.z, nq = ((re ? 2 : 5) - z0 + zn - 1) / zn;
+            auto comp = [&](int i) { return (re ? 4 : 1) * (z0 + i * zn); };
             // symmetry: the momentum component normal to a mirrored boundary changes sign
             // (mirrored on two axes: both components)
             auto msign = [&](int q) {
@@ -243,11 +255,31 @@ __global__ __launch_bounds__(TPB) void k_fill_halos(T *__restrict__ U, WorkList 
             };
             if (src >= 0) {
                 const T *sb = U + (size_t)src * 5 * CELLS_P;
-                if (mirbits == 0) {   // copies and zero-gradient clamps (uniform per workgroup)
+                if (vec && g.clamp[0] < 0) {
+                    // rows of quads (the 3-layer x-faces copy their fourth layer along): the
+                    // element-wise forms below spend 20 integer instructions on 4 bytes
+                    const int nx = (g.n[0] + 3) / 4, x0 = g.lo[0] & ~3, nrow = g.n[1] * g.n[2] * nx;
+                    const Div dr(nrow), dx(nx);
+    #pragma unroll 4
+                    for (int t = tid; t < nq * nrow; t += TPB) {
+                        const int qi = dr.quot(t), e = t - qi * nrow, q = comp(qi);
+                        const int e1 = dx.quot(e), e2 = d1.quot(e1);
+                        const int i = x0 + 4 * (e - e1 * nx), j = g.lo[1] + e1 - e2 * g.n[1], k = g.lo[2] + e2;
+                        const int sj = (mirbits & 2) ? mir_index(g, 1) - j : (g.clamp[1] >= 0 ? g.clamp[1] : j - NI * g.r[1]);
+                        const int sk = (mirbits & 4) ? mir_index(g, 2) - k : (g.clamp[2] >= 0 ? g.clamp[2] : k - NI * g.r[2]);
+                        Quad<T> v = *(const Quad<T> *)(sb + pidx(q, sk, sj, i - NI * g.r[0]));
+                        if (mirbits) {
+                            const T s = msign(q);
+    #pragma unroll
+                            for (int w = 0; w < 4; ++w) v.v[w] = s * v.v[w];
+                        }
+                        *(Quad<T> *)(dst + pidx(q, k, j, i)) = v;
+                    }
+                } else if (mirbits == 0) {   // copies and zero-gradient clamps (uniform per workgroup)
     #pragma unroll 4
                     for (int t = tid; t < nq * ncell; t += TPB) {   // unrolled: several loads in flight
                         const int qi = dc.quot(t), e = t - qi * ncell;
-                        const int q = re ? 4 * qi : qi;
+                        const int q = comp(qi);
                         const int e1 = d0.quot(e), e2 = d1.quot(e1);
                         const int i = g.lo[0] + e - e1 * g.n[0], j = g.lo[1] + e1 - e2 * g.n[1], k = g.lo[2] + e2;
                         const int si = g.clamp[0] >= 0 ? g.clamp[0] : i - NI * g.r[0];
@@ -259,7 +291,7 @@ __global__ __launch_bounds__(TPB) void k_fill_halos(T *__restrict__ U, WorkList 
     #pragma unroll 4
                     for (int t = tid; t < nq * ncell; t += TPB) {
                         const int qi = dc.quot(t), e = t - qi * ncell;
-                        const int q = re ? 4 * qi : qi;
+                        const int q = comp(qi);
                         const int e1 = d0.quot(e), e2 = d1.quot(e1);
                         const int i = g.lo[0] + e - e1 * g.n[0], j = g.lo[1] + e1 - e2 * g.n[1], k = g.lo[2] + e2;
                         const int si = (mirbits & 1) ? mir_index(g, 0) - i : (g.clamp[0] >= 0 ? g.clamp[0] : i - NI * g.r[0]);
@@ -305,13 +337,13 @@ __global__ __launch_bounds__(TPB) void k_fill_halos(T *__restrict__ U, WorkList 
                 for (int n = 0; n < NAT; ++n)
                     if (tid + n * TPB < na) av[n] = pu[q * CELLS_P + aoff[n]];
             };
-            load_a(0);
+            load_a(comp(0));
             for (int qi = 0; qi < nq; ++qi) {
-                const int q = re ? 4 * qi : qi;
+                const int q = comp(qi);
     #pragma unroll
                 for (int n = 0; n < NAT; ++n)
                     if (tid + n * TPB < na) A[tid + n * TPB] = av[n];
-                if (qi + 1 < nq) load_a(re ? 4 * (qi + 1) : qi + 1);
+                if (qi + 1 < nq) load_a(comp(qi + 1));
                 __syncthreads();
                 const int nx = np[2] * np[1] * me[0];
                 for (int t = tid; t < nx; t += TPB) {
@@ -979,12 +1011,20 @@ hipError_t launch_fill_halos(T *U, const WorkList &wl, const DevTables &tb, Fill
     // missing-faces mode measured no faster)
     const int nreg = (mode & FILL_ITEMS) ? 1 : (mode & FILL_FACES) ? 6 : 26;
     const int gy = ((mode & FILL_MISSING) && !(mode & FILL_FACES)) ? 2 : nreg;
-    const dim3 grid = grid2(round_xcd(wl.grid), gy);
+    // few regions: a workgroup per component, since one takes its time from a chain of loads and
+    // barriers per component (many regions: one for all, which shares the index arithmetic)
+    const int nz = (int64_t)wl.n * gy * 5 <= 4096 ? ((mode & FILL_RHO_E) ? 2 : 5) : 1;
+    // (a captured launch's grid is a bound: for a short list, one that loops rather than thousands
+    // of workgroups without a region)
+    const int gx = wl.desc && nz > 1 ? std::min(wl.grid, std::max(64, 2 * wl.n)) : wl.grid;
+    const dim3 grid(round_xcd(gx), gy, nz);
+    // (FP64 rows by element: two accesses per quad, 1 % slower on 360 leaves)
+    const int vec = sizeof(T) == 4 && ((uintptr_t)U & 15) == 0;
     if (tb.ext_bc)
-        hipLaunchKernelGGL((k_fill_halos<T, true>), grid, dim3(TPB), 0, st, U, wl, tb.meta, tb.nbr, (int)mode,
+        hipLaunchKernelGGL((k_fill_halos<T, true>), grid, dim3(TPB), 0, st, U, wl, tb.meta, tb.nbr, (int)mode, vec,
                            (const T *)tb.bcfix);
     else
-        hipLaunchKernelGGL((k_fill_halos<T, false>), grid, dim3(TPB), 0, st, U, wl, tb.meta, tb.nbr, (int)mode,
+        hipLaunchKernelGGL((k_fill_halos<T, false>), grid, dim3(TPB), 0, st, U, wl, tb.meta, tb.nbr, (int)mode, vec,
                            (const T *)nullptr);
     return hipGetLastError();
 }
