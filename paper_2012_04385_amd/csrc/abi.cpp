@@ -301,7 +301,7 @@ int stage_buffers(mrfv_ctx *ctx) {
 // state.
 template <typename T>
 int do_stage_fused(mrfv_ctx *ctx, int stage, const double *dt, const T *Uin, T *Uout, T *U0,
-                   bool restrict_parents = false, double *cflmax = nullptr) {
+                   bool restrict_parents = false, double *cflmax = nullptr, const T *pgb = nullptr) {
     const HostLists &L = ctx->lists;
     T *FF = (T *)ctx->d_FF;
     hipEvent_t ev{};
@@ -309,7 +309,7 @@ int do_stage_fused(mrfv_ctx *ctx, int stage, const double *dt, const T *Uin, T *
     // the fused kernel has no grid-stride loop: its grid must cover every possible leaf
     HIP_OK(launch_rhs_update<T>(flux_kernel(ctx), ctx->rhs_variant, stage, dt, Uin, Uout, U0,
                                 wlist(ctx, DESC_LEAVES, 1 << 30), ctx->tb, ctx->d_inst, FF, ctx->d_err,
-                                restrict_parents ? 1 : 0, cflmax, false, ctx->stream));
+                                restrict_parents ? 1 : 0, cflmax, false, ctx->stream, pgb));
     timing_end(ctx, ev, (int64_t)L.all_leaves_cnt * CELLS_I);
     if (ctx->has_jumps) {
         for (int l = levels_to_cover(ctx) - 1; l >= 0; --l)
@@ -610,7 +610,13 @@ int do_stages(mrfv_ctx *ctx, T *U, T *U0, T *Lb, double *dt) {
             // next step's CFL pass; the leaves whose boundary cells the jump correction then
             // changes get theirs again from the corrected state
             double *cflmax = ctx->capturing && s == 2 ? ctx->d_blockred : nullptr;
-            CALL(do_stage_fused<T>(ctx, s, dt, in, out, U0, s < 2 ? par : adapt, cflmax));
+            // Tait: every cell's power once, in an energy component that is free (the stages take
+            // the energy, which is not evolved, from U and U0): W2's for U, then the input's own
+            T *pgb = flux_kernel(ctx) != SCH_TAIT ? nullptr : s == 0 ? buf[2] : in;
+            if (pgb)
+                HIP_OK(launch_tait_pg<T>(in, pgb, wlist(ctx, par ? DESC_ALL : DESC_LEAVES), ctx->tb, ctx->d_inst,
+                                         ctx->stream));
+            CALL(do_stage_fused<T>(ctx, s, dt, in, out, U0, s < 2 ? par : adapt, cflmax, pgb));
             if (cflmax && ctx->has_jumps)
                 HIP_OK(launch_cfl_blocks<T>(out, wlist(ctx, DESC_JCORR), ctx->tb, ctx->d_inst,
                                                 ctx->d_blockred, ctx->stream));

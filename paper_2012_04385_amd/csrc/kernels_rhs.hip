@@ -432,11 +432,18 @@ __device__ __forceinline__ double expm1_(double x) { return expm1(x); }
 __device__ __forceinline__ float log1p_(float x) { return log1pf(x); }
 __device__ __forceinline__ double log1p_(double x) { return log1p(x); }
 
+// A face's six powers were half of its instructions, and a cell's is needed by up to eighteen
+// faces: before a fused stage k_tait_pg writes every cell's once, into the energy components of
+// an array laid out as the state (a step on a four-level tube's tree: 700 -> 590 us).
 template <typename T>
-__device__ __forceinline__ void derive_state(const TaitGas<T> &G, TaitState<T> &s) {
+__device__ __forceinline__ T tait_pg(T r, const TaitGas<T> &G) {
+    return pow_(r * G.ir0, G.g);
+}
+
+template <typename T>
+__device__ __forceinline__ void derive_state(const TaitGas<T> &G, TaitState<T> &s) {   // s.pg set
     s.ir = rcp_(s.r);
     s.un = s.mn * s.ir;
-    s.pg = pow_(s.r * G.ir0, G.g);
     s.p = fma(G.B, s.pg - (T)1, G.A);
     s.c = sqrt_(G.g * G.B * s.pg * s.ir);
 }
@@ -499,6 +506,27 @@ struct Phys<T, SCH_TAIT_ROE_WENO5> {
         return Eos{(T)P.gamma, (T)P.B, (T)P.tait_A, (T)(1.0 / P.tait_rho0)};
     }
 };
+
+// Tait: energy components of Pg (laid out as U; may be U) <- (rho/rho0)^gamma of U's interior
+// and, on leaves, face halos, z-plane blockIdx.y.  Reads and writes one component.
+template <typename T>
+__global__ __launch_bounds__(TPB) void k_tait_pg(const T *U, T *Pg, WorkList wl,
+                                                 const BlockMeta *__restrict__ meta,
+                                                 const InstDev *__restrict__ inst) {
+    const int nb = wl.count(), z = blockIdx.y;
+    const int zout = z >= HW && z < HW + NI ? 0 : 1;
+    for (int b = blockIdx.x; b < nb; b += gridDim.x) {
+        const int slot = wl.at(b);
+        const BlockMeta m = meta[slot];
+        const TaitGas<T> G = Phys<T, SCH_TAIT_ROE_WENO5>::eos(inst[m.inst]);
+        const size_t o = (size_t)slot * 5 * CELLS_P + z * NP * NP;
+        for (int c = threadIdx.x; c < NP * NP; c += TPB) {
+            const int y = c / NP, x = c - y * NP;
+            const int out = zout + (y >= HW && y < HW + NI ? 0 : 1) + (x >= HW && x < HW + NI ? 0 : 1);
+            if (out <= m.leaf) Pg[o + 4 * CELLS_P + c] = tait_pg(U[o + c], G);
+        }
+    }
+}
 
 // Non-leaf blocks: face-flux planes <- area average of the children's planes.
 template <typename T>
@@ -680,7 +708,7 @@ enum { RHS_FORCE_PTR = 1, RHS_OWN_HALO = 2 };
 // read through one buffer resource (range-checked: out-of-range reads return zero);
 // usable (near) when the own block and its six face neighbours lie within 4 GiB.
 struct NearSrc {
-    __amdgpu_buffer_rsrc_t rsrc;
+    __amdgpu_buffer_rsrc_t rsrc, pg;   // pg (Tait): the same cells of the array with the powers
     unsigned own, lo[3], hi[3];
     bool near;
 };
@@ -701,7 +729,8 @@ __device__ __forceinline__ T buffer_ld(__amdgpu_buffer_rsrc_t r, unsigned voff, 
 template <typename T, int D, int SCH, class Source>
 __device__ __forceinline__ void face_flux_at(const T *__restrict__ ub, const Source &source,
                                              const NearSrc &ns, int base, int pos0,
-                                             const typename Phys<T, SCH>::Eos &G, T Fp[5]) {
+                                             const typename Phys<T, SCH>::Eos &G,
+                                             const T *__restrict__ Uin, const T *pgb, T Fp[5]) {
     constexpr int stride = Axes<D>::STRIDE;
     constexpr int n1 = Axes<D>::N1, t1 = Axes<D>::T1, t2 = Axes<D>::T2;   // rotated components
     constexpr bool ENERGY = SCH != SCH_TAIT_ROE_WENO5;
@@ -716,6 +745,7 @@ __device__ __forceinline__ void face_flux_at(const T *__restrict__ ub, const Sou
             w[j].mt1 = buffer_ld<T>(ns.rsrc, off, t1 * CB);
             w[j].mt2 = buffer_ld<T>(ns.rsrc, off, t2 * CB);
             if constexpr (ENERGY) w[j].E = buffer_ld<T>(ns.rsrc, off, 4 * CB);
+            else w[j].pg = pgb ? buffer_ld<T>(ns.pg, off, 4 * CB) : (T)0;
         };
         if (__all(pos0 >= HW && pos0 + 5 < HW + NI)) {
 #pragma unroll
@@ -742,7 +772,13 @@ __device__ __forceinline__ void face_flux_at(const T *__restrict__ ub, const Sou
             w[j].mt1 = u[t1 * CELLS_P];
             w[j].mt2 = u[t2 * CELLS_P];
             if constexpr (ENERGY) w[j].E = u[4 * CELLS_P];
+            else w[j].pg = pgb ? pgb[(src - Uin) + base + j * stride + 4 * CELLS_P] : (T)0;
         }
+    }
+    if constexpr (!ENERGY) {
+        if (!pgb)
+#pragma unroll
+            for (int j = 0; j < 6; ++j) w[j].pg = tait_pg(w[j].r, G);
     }
     // the arithmetic follows the loads in one place for both load paths
 #pragma unroll
@@ -772,7 +808,7 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
                                                       const InstDev *__restrict__ inst, T *FF,
                                                       int32_t *err, int restrict_parents,
                                                       double *__restrict__ cflmax, int flags,
-                                                      int nsl) {
+                                                      int nsl, const T *pgb) {
     constexpr int NFX = GP * NI * (NI + 1);   // x-faces per group (y-faces alike)
     // x- and y-faces are numbered with the faces 3 .. 13 of each row first: their
     // six-cell stencils lie in the own interior, so whole wavefronts of them take the
@@ -842,6 +878,10 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
         ns.rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(ub - ((uintptr_t)ub - mn) / sizeof(T)),
                                                     (short)0, ns.near ? (int)(unsigned)span : 0,
                                                     BUFFER_RSRC_WORD3);
+        if constexpr (SCH == SCH_TAIT_ROE_WENO5)
+            ns.pg = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)((pgb ? pgb : Uin) + (ub - Uin) - ((uintptr_t)ub - mn) / sizeof(T)), (short)0,
+                ns.near ? (int)(unsigned)span : 0, BUFFER_RSRC_WORD3);
         ns.own = (unsigned)((uintptr_t)ub - mn);
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -891,7 +931,9 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
             T un[5], us[5], lq[5];
 #pragma unroll
             for (int q = 0; q < 5; ++q) {
-                us[q] = ub[o + q * CELLS_P];
+                // Tait: the energy is not evolved, and after the first stage pg may stand there
+                us[q] = SCH == SCH_TAIT_ROE_WENO5 && q == 4 && pgb && stage > 0 ? u0b[q * CELLS_I + c]
+                                                                                : ub[o + q * CELLS_P];
                 lq[q] = -D[p][q] * inv_dx;
             }
             if (P.has_source) add_source(P, us, lq);   // uniform per workgroup
@@ -1006,7 +1048,7 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
                 p = v / (NF_OUT * NI);
             }
             const int base = ((k0 + p + HW) * NP + y + HW) * NP + f + 1;
-            face_flux_at<T, 0, SCH>(ub, source, ns, base, f + 1, G, F);
+            face_flux_at<T, 0, SCH>(ub, source, ns, base, f + 1, G, Uin, pgb, F);
 #pragma unroll
             for (int q = 0; q < 5; ++q) Fx[buf][p][y][f][q] = F[q];
             if (f == 0 || f == NI) {
@@ -1026,7 +1068,7 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
                 p = v / (NI * NF_OUT);
             }
             const int base = ((k0 + p + HW) * NP + f + 1) * NP + x + HW;
-            face_flux_at<T, 1, SCH>(ub, source, ns, base, f + 1, G, F);
+            face_flux_at<T, 1, SCH>(ub, source, ns, base, f + 1, G, Uin, pgb, F);
 #pragma unroll
             for (int q = 0; q < 5; ++q) Fy[buf][p][f][x][q] = F[q];
             if (f == 0 || f == NI) {
@@ -1037,7 +1079,7 @@ void k_rhs_update(int stage, const double *__restrict__ dt,
             const int x = t % NI, y = (t / NI) % NI;
             const int kf = k0 + t / NFZ + (ch.below ? 0 : 1);   // face between interior planes kf-1 and kf
             const int base = ((kf + 1) * NP + y + HW) * NP + x + HW;   // padded z = kf+1 .. kf+6
-            face_flux_at<T, 2, SCH>(ub, source, ns, base, kf + 1, G, F);
+            face_flux_at<T, 2, SCH>(ub, source, ns, base, kf + 1, G, Uin, pgb, F);
 #pragma unroll
             for (int q = 0; q < 5; ++q) Fz[kf % NZR][y][x][q] = F[q];
             if (kf == 0 || kf == NI) {
@@ -1189,6 +1231,14 @@ __global__ __launch_bounds__(TPB) void k_reflux_update(int stage, const double *
 }  // namespace
 
 template <typename T>
+hipError_t launch_tait_pg(const T *U, T *Pg, const WorkList &wl, const DevTables &tb, const InstDev *inst,
+                          hipStream_t st) {
+    if (wl.grid <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_tait_pg<T>, dim3(wl.grid, NP), dim3(TPB), 0, st, U, Pg, wl, tb.meta, inst);
+    return hipGetLastError();
+}
+
+template <typename T>
 hipError_t launch_ff_restrict(T *FF, const WorkList &wl, const DevTables &tb, hipStream_t st) {
     if (wl.grid <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_ff_restrict<T>, dim3(wl.grid, 6), dim3(TPB), 0, st, FF, wl, tb.child);
@@ -1240,7 +1290,8 @@ int rhs_slabs(int nleaf) { return slab_split(nleaf, 8, true); }
 template <typename T, int G, int B, bool PS, int WP, int SCH>
 static void launch_shape(int stage, const double *dt, const T *Uin, T *Uout, T *U0, const WorkList &wl,
                          const DevTables &tb, const InstDev *inst, T *FF, int32_t *err,
-                         int restrict_parents, double *cflmax, int flags, hipStream_t st) {
+                         int restrict_parents, double *cflmax, int flags, hipStream_t st,
+                         const T *pgb = nullptr) {
     // every slab of every leaf: exactly (eager), or (captured) for any number of leaves with
     // this split up to the list's bound
     constexpr int MAX_SLABS = std::min(NI / G, 8);
@@ -1249,7 +1300,7 @@ static void launch_shape(int stage, const double *dt, const T *Uin, T *Uout, T *
     const int grid = PS ? std::min(items, persist_grid(B)) : round_xcd(items);
     hipLaunchKernelGGL((k_rhs_update<T, G, B, PS, WP, SCH>), dim3(grid), dim3(B), 0, st, stage, dt, Uin,
                        Uout, U0, wl, tb.meta, tb.nbr, inst, FF, err, restrict_parents, cflmax, flags,
-                       nsl);
+                       nsl, pgb);
 }
 
 template <int V, int SCH>
@@ -1297,7 +1348,7 @@ template <typename T>
 hipError_t launch_rhs_update(int scheme, int variant, int stage, const double *dt, const T *Uin,
                              T *Uout, T *U0, const WorkList &wl, const DevTables &tb,
                              const InstDev *inst, T *FF, int32_t *err, int restrict_parents,
-                             double *cflmax, bool own_halo, hipStream_t st) {
+                             double *cflmax, bool own_halo, hipStream_t st, const T *pgb) {
     if (wl.grid <= 0) return hipSuccess;
     if (Uin == Uout) return hipErrorInvalidValue;   // neighbours' interiors are read
     if (stage == RHS_TO_L && restrict_parents) return hipErrorInvalidValue;
@@ -1309,13 +1360,13 @@ hipError_t launch_rhs_update(int scheme, int variant, int stage, const double *d
             case SCH_ROE_TENO5: launch_shape<T, F64_GP, F64_TPB, false, 1, SCH_ROE_TENO5>(MRFV_ARGS); break;
             case SCH_LLF_WENO5: launch_shape<T, F64_GP, F64_TPB, false, 1, SCH_LLF_WENO5>(MRFV_ARGS); break;
             case SCH_HLLC_WAO53: launch_shape<T, F64_GP, F64_TPB, false, 1, SCH_HLLC_WAO53>(MRFV_ARGS); break;
-            case SCH_TAIT_ROE_WENO5: launch_shape<T, F64_GP, F64_TPB, false, 1, SCH_TAIT_ROE_WENO5>(MRFV_ARGS); break;
+            case SCH_TAIT_ROE_WENO5: launch_shape<T, F64_GP, F64_TPB, false, 1, SCH_TAIT_ROE_WENO5>(MRFV_ARGS, pgb); break;
             default: return hipErrorInvalidValue;
         }
         return hipGetLastError();
     } else {
     if (scheme == SCH_TAIT_ROE_WENO5) {
-        launch_shape<T, 2, 512, false, 1, SCH_TAIT_ROE_WENO5>(MRFV_ARGS);
+        launch_shape<T, 2, 512, false, 1, SCH_TAIT_ROE_WENO5>(MRFV_ARGS, pgb);
         return hipGetLastError();
     }
     if (variant < 0 || variant >= rhs_variants(scheme)) return hipErrorInvalidValue;
@@ -1361,7 +1412,10 @@ hipError_t launch_reflux_update(int stage, const double *dt, T *U, const T *FF,
 #define MRFV_INST_RHS(T)                                                                    \
     template hipError_t launch_rhs_update<T>(int, int, int, const double *, const T *, T *, T *, \
                                              const WorkList &, const DevTables &, const InstDev *, \
-                                             T *, int32_t *, int, double *, bool, hipStream_t); \
+                                             T *, int32_t *, int, double *, bool, hipStream_t, \
+                                             const T *); \
+    template hipError_t launch_tait_pg<T>(const T *, T *, const WorkList &, const DevTables &, const InstDev *, \
+                                          hipStream_t);                                     \
     template hipError_t launch_ff_restrict<T>(T *, const WorkList &, const DevTables &,     \
                                               hipStream_t);                                 \
     template hipError_t launch_reflux<T>(T *, const T *, const WorkList &, const DevTables &, \

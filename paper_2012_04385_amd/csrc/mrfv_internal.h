@@ -315,7 +315,13 @@ template <typename T>
 hipError_t launch_rhs_update(int scheme, int variant, int stage, const double *dt, const T *Uin,
                              T *Uout, T *U0, const WorkList &leaves, const DevTables &tb,
                              const InstDev *inst, T *FF, int32_t *err, int restrict_parents,
-                             double *cflmax, bool own_halo, hipStream_t st);
+                             double *cflmax, bool own_halo, hipStream_t st, const T *pgb = nullptr);
+// Tait: (rho/rho0)^gamma of the listed blocks' interiors (and the leaves' face halos) of U into
+// the energy components of Pg, an array laid out as U (or U itself), as launch_rhs_update reads
+// them through pgb.  Null there: the faces compute their own.
+template <typename T>
+hipError_t launch_tait_pg(const T *U, T *Pg, const WorkList &wl, const DevTables &tb, const InstDev *inst,
+                          hipStream_t st);
 int rhs_slabs(int nleaf);   // workgroups per leaf of a launch over nleaf leaves
 int rhs_variants(int scheme);
 int rhs_default_variant(int scheme);   // the shape fastest on the measured trees

@@ -64,3 +64,27 @@ def test_stages_fused_and_through_l_agree(dtype, eos):
     sa, sb = a.leaf_states(), b.leaf_states()
     assert set(sa) == set(sb)
     assert max(np.abs(sa[k] - sb[k]).max() for k in sa) <= tol
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("adapt", [0, 1])
+def test_tait_keeps_the_energies_it_is_given(dtype, adapt):
+    """Tait's equation evolves no energy; its stages pass the cells' powers of the density
+    through a free energy component.  The caller's energies come back bit for bit, and the
+    rest of the state is what it is with zero energies."""
+    import torch
+    from paper_2012_04385_amd.mrfv import Solver
+    pb = W.sod_tait_mr3()
+    pb.lmax, pb.eps = 2, 0.1 * pb.eps
+    zero = Solver([pb], dtype=dtype, batched=0, adapt=adapt).init()
+    some = Solver([pb], dtype=dtype, batched=0, adapt=adapt).init()
+    some.U[:, 4] = 0.75                 # whole blocks: halos, parents and averages hold it too
+    for _ in range(2):
+        zero.step()
+        some.step()
+        some.check()
+    sz, ss = zero.leaf_states(), some.leaf_states()
+    assert set(sz) == set(ss)
+    for k in sz:
+        assert np.array_equal(sz[k][:4], ss[k][:4]), k
+        assert (ss[k][4] == 0.75).all() and (sz[k][4] == 0).all(), k
