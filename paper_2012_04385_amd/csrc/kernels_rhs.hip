@@ -30,9 +30,12 @@ namespace {
 constexpr int TPB = 256;
 
 __device__ __forceinline__ float rcp_(float x) { return __builtin_amdgcn_rcpf(x); }
-// FP64: the hardware's estimate (about 28 bits) and two Newton steps, 5 instructions against
-// the 11 of an IEEE division; within one unit in the last place for the normal numbers these
-// kernels meet (densities, sums of square roots, products of smoothness indicators >= 1e-24).
+// FP64: the hardware's estimate (2^-24.4 at worst) and two Newton steps, 5 instructions against
+// the 11 of an IEEE division.  For the normal numbers these kernels meet (densities, sums of
+// square roots, products of smoothness indicators >= 1e-24) rcp_, sqrt_ and their composition
+// rsqrt_ round as 1 / x, sqrt(x) and 1 / sqrt(x) do: the same in 5e8 draws from 1e-24 to 1e6.
+// A Newton rsqrt of its own, one unit off at times, moved gas at rest by 1e-17 and with it the
+// side some faces take their flux from: 1e-8 in the solution after a few steps.
 __device__ __forceinline__ double rcp_(double x) {
     double r = __builtin_amdgcn_rcp(x);
     r = fma(r, fma(-x, r, 1.0), r);
@@ -50,11 +53,7 @@ __device__ __forceinline__ double sqrt_(double x) {   // x >= 0, Newton on the e
     return x == 0.0 ? x : g;
 }
 __device__ __forceinline__ float rsqrt_(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double rsqrt_(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
-    return fma(0.5 * y, fma(-x * y, y, 1.0), y);
-}
+__device__ __forceinline__ double rsqrt_(double x) { return rcp_(sqrt_(x)); }
 
 template <typename T>
 struct Gas {
