@@ -433,7 +433,7 @@ __device__ __forceinline__ double log1p_(double x) { return log1p(x); }
 
 // A face's six powers were half of its instructions, and a cell's is needed by up to eighteen
 // faces: before a fused stage k_tait_pg writes every cell's once, into the energy components of
-// an array laid out as the state (a step on a four-level tube's tree: 700 -> 590 us).
+// an array laid out as the state (a step on a four-level tube's tree: 700 -> 565 us).
 template <typename T>
 __device__ __forceinline__ T tait_pg(T r, const TaitGas<T> &G) {
     return pow_(r * G.ir0, G.g);
@@ -506,27 +506,6 @@ struct Phys<T, SCH_TAIT_ROE_WENO5> {
     }
 };
 
-// Tait: energy components of Pg (laid out as U; may be U) <- (rho/rho0)^gamma of U's interior
-// and, on leaves, face halos, z-plane blockIdx.y.  Reads and writes one component.
-template <typename T>
-__global__ __launch_bounds__(TPB) void k_tait_pg(const T *U, T *Pg, WorkList wl,
-                                                 const BlockMeta *__restrict__ meta,
-                                                 const InstDev *__restrict__ inst) {
-    const int nb = wl.count(), z = blockIdx.y;
-    const int zout = z >= HW && z < HW + NI ? 0 : 1;
-    for (int b = blockIdx.x; b < nb; b += gridDim.x) {
-        const int slot = wl.at(b);
-        const BlockMeta m = meta[slot];
-        const TaitGas<T> G = Phys<T, SCH_TAIT_ROE_WENO5>::eos(inst[m.inst]);
-        const size_t o = (size_t)slot * 5 * CELLS_P + z * NP * NP;
-        for (int c = threadIdx.x; c < NP * NP; c += TPB) {
-            const int y = c / NP, x = c - y * NP;
-            const int out = zout + (y >= HW && y < HW + NI ? 0 : 1) + (x >= HW && x < HW + NI ? 0 : 1);
-            if (out <= m.leaf) Pg[o + 4 * CELLS_P + c] = tait_pg(U[o + c], G);
-        }
-    }
-}
-
 // Non-leaf blocks: face-flux planes <- area average of the children's planes.
 template <typename T>
 __global__ __launch_bounds__(TPB) void k_ff_restrict(T *FF, WorkList wl,
@@ -561,6 +540,40 @@ __device__ __forceinline__ int face_region(int side) {
     int r[3] = {0, 0, 0};
     r[d] = s;
     return (r[2] + 1) * 9 + (r[1] + 1) * 3 + (r[0] + 1);
+}
+
+// Tait: energy components of Pg (laid out as U; may be U) <- (rho/rho0)^gamma of U's interior
+// and, on leaves, of the face halos that the faces read, z-plane blockIdx.y.  Bound by pow's
+// instructions: with every face halo 21 us on 338 leaves, without those beside same-level
+// neighbours (read in place) 13.6.
+template <typename T>
+__global__ __launch_bounds__(FACE) void k_tait_pg(const T *U, T *Pg, WorkList wl,
+                                                  const BlockMeta *__restrict__ meta,
+                                                  const int32_t *__restrict__ nbr,
+                                                  const InstDev *__restrict__ inst) {
+    const int nb = wl.count(), z = blockIdx.y, t = threadIdx.x;
+    for (int b = blockIdx.x; b < nb; b += gridDim.x) {
+        const int slot = wl.at(b);
+        const BlockMeta m = meta[slot];
+        auto reads_halo = [&](int side) {   // as the faces choose their sources
+            return m.leaf && (((m.zg >> side) & 1) || nbr[(size_t)slot * 27 + face_region(side)] < 0);
+        };
+        if (z == 0 || z == NP - 1) continue;   // the faces read three layers of four
+        if ((z < HW && !reads_halo(4)) || (z >= HW + NI && !reads_halo(5))) continue;
+        const TaitGas<T> G = Phys<T, SCH_TAIT_ROE_WENO5>::eos(inst[m.inst]);
+        const size_t o = (size_t)slot * 5 * CELLS_P + z * NP * NP;
+        auto cell = [&](int y, int x) {
+            const size_t c = o + y * NP + x;
+            Pg[c + 4 * CELLS_P] = tait_pg(U[c], G);
+        };
+        cell(t / NI + HW, t % NI + HW);
+        if (z < HW || z >= HW + NI) continue;
+        const int side = t / 64, k = t % 64;   // a wavefront per x or y side
+        if (k >= 3 * NI || !reads_halo(side)) continue;
+        const int far = side & 1 ? HW + NI : 1;
+        if (side < 2) cell(k / 3 + HW, far + k % 3);
+        else cell(far + k / NI, k % NI + HW);
+    }
 }
 
 // Coarse leaves at resolution jumps: replace the own boundary flux by the fine average in
@@ -1233,7 +1246,7 @@ template <typename T>
 hipError_t launch_tait_pg(const T *U, T *Pg, const WorkList &wl, const DevTables &tb, const InstDev *inst,
                           hipStream_t st) {
     if (wl.grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_tait_pg<T>, dim3(wl.grid, NP), dim3(TPB), 0, st, U, Pg, wl, tb.meta, inst);
+    hipLaunchKernelGGL(k_tait_pg<T>, dim3(wl.grid, NP), dim3(FACE), 0, st, U, Pg, wl, tb.meta, tb.nbr, inst);
     return hipGetLastError();
 }
 
