@@ -192,7 +192,7 @@ int do_fill(mrfv_ctx *ctx, T *U, int max_level, int mode = FILL_ALL, bool with_p
         if (m == FILL_MISSING_FACES) {
             // a stage: the parents' regions its predictions read and the leaves' faces
             HIP_OK(launch_fill_halos<T>(U, wlist(ctx, desc_fitem(l), 4096), ctx->tb, (FillMode)(FILL_ITEMS | qsel), ctx->stream));
-        } else if (m == FILL_ALL) {
+        } else if (m == FILL_ALL || m == FILL_VISC) {
             HIP_OK(launch_fill_halos<T>(U, wlist(ctx, desc_lvl(l), 1024), ctx->tb, (FillMode)mode,
                                         ctx->stream));
         } else {
@@ -623,12 +623,12 @@ int do_stages(mrfv_ctx *ctx, T *U, T *U0, T *Lb, double *dt) {
         }
         return MRFV_OK;
     }
-    // stages through L and an update in place; the viscous fluxes read the edge halos too
-    const int fill = ctx->viscous ? FILL_ALL : FILL_FACES;
+    // stages through L and an update in place
+    const int fill = ctx->viscous ? FILL_VISC : FILL_FACES;
     for (int s = 0; s < 3; ++s) {
         CALL(do_project<T>(ctx, U));
         CALL(do_fill<T>(ctx, U, 1 << 20, fill));
-        CALL(do_rhs<T>(ctx, U, Lb, true));
+        CALL(do_rhs<T>(ctx, U, Lb, !ctx->viscous));
         CALL(do_update<T>(ctx, s, dt, U, U0, Lb));
     }
     return MRFV_OK;

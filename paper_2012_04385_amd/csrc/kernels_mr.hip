@@ -206,7 +206,9 @@ __global__ __launch_bounds__(TPB) void k_fill_halos(T *__restrict__ U, WorkList 
         const BlockMeta m = meta[slot];
         // regions blockIdx.y, blockIdx.y + gridDim.y, ... of the block, or the item's
         for (int ridx = items ? item_reg : blockIdx.y; ridx < (items ? item_reg + 1 : nreg); ridx += gridDim.y) {
-            const Region g = make_region(faces, ridx, EXT ? m.zg : (m.zg & 63));
+            Region g = make_region(faces, ridx, EXT ? m.zg : (m.zg & 63));
+            const bool visc = (mode & FILL_VISC) && m.leaf;
+            if (visc && g.n[0] + g.n[1] + g.n[2] == 3 * HW) continue;   // corner
             // mirrored axes as bits (no run-time indexing into the region's arrays, which would
             // put them in scratch memory)
             const int mirbits = EXT ? g.mirbits : 0;
@@ -241,6 +243,13 @@ __global__ __launch_bounds__(TPB) void k_fill_halos(T *__restrict__ U, WorkList 
             const int src = own ? slot : nbr[(size_t)slot * 27 + (g.r[2] + 1) * 9 + (g.r[1] + 1) * 3 + (g.r[0] + 1)];
             if ((mode & FILL_MISSING) && src >= 0 && !clamped) continue;   // read in place
             if ((mode & FILL_PRESENT) && src < 0) continue;                // keeps its values
+            if (visc && src >= 0 && !clamped)
+#pragma unroll
+                for (int a = 0; a < 3; ++a)
+                    if (g.n[a] == HW) {
+                        g.lo[a] += g.lo[a] < HW ? HW - 1 : 0;
+                        g.n[a] = 1;
+                    }
             T *dst = U + (size_t)slot * 5 * CELLS_P;
             const int ncell = g.n[0] * g.n[1] * g.n[2];
             const Div dc(ncell), d0(g.n[0]), d1(g.n[1]);

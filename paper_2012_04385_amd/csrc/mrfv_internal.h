@@ -226,8 +226,11 @@ constexpr int N_DESC = 5 + DESC_PER_LEVEL * MAX_LEVELS;
 // nothing else).  FILL_PRESENT (with FILL_FACES) copies only: faces without a same-level
 // neighbour keep their values (the integrated jump halos of local time stepping).
 // FILL_ITEMS: the list holds one item per region (desc_fitem) instead of blocks.
+// FILL_VISC (all regions): what a viscous stage reads of a leaf's halo.  The viscous fluxes
+// take one layer of the faces and edges, the convective ones read same-level neighbours in
+// place, nothing reads a leaf's corners: copies are one layer deep and corners left out.
 enum FillMode { FILL_ALL = 0, FILL_FACES = 1, FILL_MISSING = 2, FILL_MISSING_FACES = 3, FILL_RHO_E = 4,
-                FILL_PRESENT = 8, FILL_ITEMS = 16 };
+                FILL_PRESENT = 8, FILL_ITEMS = 16, FILL_VISC = 32 };
 
 // --------------------------------------------------------------- kernel launchers ----
 // All launchers enqueue on `st` and return hipGetLastError().

@@ -88,3 +88,39 @@ def test_tait_keeps_the_energies_it_is_given(dtype, adapt):
     for k in sz:
         assert np.array_equal(sz[k][:4], ss[k][:4]), k
         assert (ss[k][4] == 0.75).all() and (sz[k][4] == 0).all(), k
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("kind", ["rti", "jumps"])
+def test_viscous_stages_need_only_the_halos_they_fill(dtype, kind):
+    """A viscous stage fills one layer of the halos beside same-level neighbours and no corner
+    of a leaf.  From a state whose halos are all NaN a step gives bit for bit what the public
+    operators give, which fill every halo and read no neighbour in place."""
+    import torch
+    from paper_2012_04385_amd.mrfv import HW, NI, Solver
+    if kind == "rti":
+        pb = W.rti(k=2.0, lmax=2, long_blocks=2)     # symmetry and fixed-value sides
+    else:
+        pb = W.sod_tait_mr3(eos="stiffened")         # zero-gradient and periodic sides
+        pb.lmax, pb.mu = 2, 1e-3
+    a = Solver([pb], dtype=dtype, batched=0, adapt=0).init()
+    b = Solver([pb], dtype=dtype, batched=0, adapt=0).init()
+    levels = {int(r[2]) for r in a.blocks() if r[6] == 1}
+    assert len(levels) >= 2
+    inner = a.U[:, :, HW:HW + NI, HW:HW + NI, HW:HW + NI].clone()
+    a.U.fill_(float("nan"))
+    a.U[:, :, HW:HW + NI, HW:HW + NI, HW:HW + NI] = inner
+    a.step()
+    b.cfl_dt()
+    for stage in range(3):
+        b.mr_project()
+        b.fill_halos()
+        b.rhs_stage()
+        b.rk_update(stage)
+    a.check()
+    b.check()
+    assert torch.equal(a.dt, b.dt)
+    sa, sb = a.leaf_states(), b.leaf_states()
+    assert set(sa) == set(sb)
+    for k in sa:
+        assert np.array_equal(sa[k], sb[k]), k
