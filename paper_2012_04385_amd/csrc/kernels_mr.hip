@@ -1019,7 +1019,11 @@ hipError_t launch_fill_halos(T *U, const WorkList &wl, const DevTables &tb, Fill
     // each (0.42 -> 0.38 ms per step of config 5; one workgroup per block in the stages'
     // missing-faces mode measured no faster)
     const int nreg = (mode & FILL_ITEMS) ? 1 : (mode & FILL_FACES) ? 6 : 26;
-    const int gy = ((mode & FILL_MISSING) && !(mode & FILL_FACES)) ? 2 : nreg;
+    // (short lists: as many more as make two thousand workgroups with two components, a region's
+    // chain of loads being what they wait for: two steps of the four-level Rayleigh-Taylor tree
+    // 3160 -> 3085 us, four of the Tait tube's 2295 -> 2215; twice as many workgroups made
+    // Kelvin-Helmholtz's longer lists 1 % slower, half as many gave half of it)
+    const int gy = ((mode & FILL_MISSING) && !(mode & FILL_FACES)) ? std::clamp(1024 / std::max(1, wl.n), 2, 26) : nreg;
     // few regions: a workgroup per component, since one takes its time from a chain of loads and
     // barriers per component (many regions: one for all, which shares the index arithmetic)
     const int nz = (int64_t)wl.n * gy * 5 <= 4096 ? ((mode & FILL_RHO_E) ? 2 : 5) : 1;
