@@ -335,7 +335,7 @@ def lts_oracle_sample():
 
 def eos_leg(warmup, steps):
     """The Sod tube of Sec. "Influence of Equation of State" (l_max 3) with Tait's equation
-    and with the stiffened gas, plain kernels, FP32 and FP64: cell-updates per second and
+    and with the stiffened gas, unbatched contexts, FP32 and FP64: cell-updates per second and
     their ratio (Tait evolves four of the five components)."""
     from paper_2012_04385_amd import workloads as W
     out = {"workload": "sod tube, 256 cells effective along x, l_max 3", "path": "plain per-block kernels",
@@ -370,7 +370,7 @@ def eos_leg(warmup, steps):
 def rti_leg(ks, t_end, dtype="f64"):
     """The Rayleigh-Taylor growth-rate study (Sec. "Rayleigh-Taylor instability") at the
     settings of its table of inputs for Atwood number 0.5 (l_max 3, 128 cells per
-    wavelength, 1:10 domain, amplitude 0.05 / k), viscous plain kernels: per wavenumber the
+    wavelength, 1:10 domain, amplitude 0.05 / k), viscous unbatched contexts: per wavenumber the
     growth rate n = d/dt ln(d / d0), fitted over 3 / sqrt(k) <= t <= t_end / sqrt(k) (past the
     start-up transient, before the amplitude leaves the linear regime), against the root of
     eq:SinglePhaseGrowth, and the solver's rate in cell-updates per second."""
@@ -496,11 +496,11 @@ def main():
     ap.add_argument("--lts-macro-steps", type=int, default=2)
     ap.add_argument("--eos-compare", action="store_true",
                     help="only run the Sod tube with Tait's equation against the stiffened gas "
-                         "(plain kernels)")
+                         "(unbatched contexts)")
     ap.add_argument("--schemes", action="store_true",
                     help="only run the four flux kernels on the weak-scaling blast (Sec. \"Weak Scaling\")")
     ap.add_argument("--rti", action="store_true",
-                    help="only run the Rayleigh-Taylor growth-rate study (viscous plain kernels)")
+                    help="only run the Rayleigh-Taylor growth-rate study (viscous, unbatched)")
     ap.add_argument("--rti-k", default="1", help="comma-separated wavenumbers of --rti")
     ap.add_argument("--rti-t-end", type=float, default=4.5,
                     help="end of the run and of the fit window, in units of 1/sqrt(k)")
@@ -582,7 +582,7 @@ def main():
         log(f"[bench] FP64 plain: {v64:.4e} cell-updates/s")
         extra.update({"fp64_plain_value": v64, "speedup_vs_fp64_plain": value / v64})
         # the baseline's own roofline: the same FLOP model per cell-update over the whole
-        # step's rate (an upper bound on the plain path's flux kernel rate) against FP64 peak
+        # step's rate (an upper bound on the flux kernel rate) against FP64 peak
         fpc64 = flops_per_cell_update(res.get("llf", 0.5))
         extra["fp64_plain_roofline"] = {"bound": "alu", "achieved": v64 * fpc64 / 1e12,
                                         "peak": PEAK_FP64_VECTOR / 1e12, "unit": "TFLOP/s",

@@ -1083,12 +1083,12 @@ int mrfv_create(mrfv_ctx **out, const mrfv_config *cfg, const mrfv_instance *ins
     }
     if (inst[0].eos == MRFV_TAIT &&
         (cfg->scheme != MRFV_ROE_WENO5 || (cfg->batched && cfg->dtype == MRFV_F32))) {
-        ctx->err = "Tait's equation runs on the plain kernels with the Roe-WENO5 flux";
+        ctx->err = "Tait's equation takes the Roe-WENO5 flux and no batched FP32 context";
         return bail(MRFV_EINVAL);
     }
     for (int i = 0; i < cfg->n_instances; ++i) ctx->viscous = ctx->viscous || inst[i].mu > 0.0;
     if (ctx->viscous && cfg->batched && cfg->dtype == MRFV_F32) {
-        ctx->err = "the viscous terms run on the plain kernels, not on the fused FP32 path";
+        ctx->err = "the viscous terms take no batched FP32 context";
         return bail(MRFV_EINVAL);
     }
     ctx->stream = (hipStream_t)hip_stream;

@@ -669,7 +669,7 @@ __global__ __launch_bounds__(TPB) void k_update(int stage, const double *__restr
     }
 }
 
-// ---------------------------------------------------------------- batched path -------
+// ---------------------------------------------------------------- fused stage --------
 
 // One workgroup per leaf, or per slab of a leaf's planes where the leaves alone leave CUs idle
 // (slab_split: 8 leaves, ten steps, 3130 -> 988 us; 592 leaves with the HLLC kernel 3150 -> 2818
