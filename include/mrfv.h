@@ -115,12 +115,16 @@ typedef struct {
     int32_t n_instances;    /* >= 1                                                     */
     int32_t slot_capacity;  /* maximum number of blocks over all instances              */
     int32_t batched;        /* every context integrates all leaves of all levels and
-                               instances in one fused rhs + update launch per stage (two
-                               more state buffers of mrfv_state_bytes; viscous contexts, and
-                               ones for which that memory is not there, take an rhs and an
-                               update launch);
+                               instances in one fused rhs + update launch per stage, through
+                               two more state buffers of mrfv_state_bytes each.  Contexts with
+                               batched and MRFV_F32 allocate them in mrfv_create; the others
+                               in their first global step outside a stream capture, if half
+                               of the device's memory stays free then (mrfv_step_lts gives
+                               them back where it needs the memory).  Without them, and in
+                               viscous contexts, a stage is an rhs and an update launch
+                               through L; mrfv_last_error says so when they were refused.
                                1: with MRFV_F32 also the entry points that need the two
-                               buffers at creation (mrfv_fused_stage, mrfv_autotune);
+                               buffers (mrfv_fused_stage, mrfv_autotune);
                                2: as 1, with the CFL step and the three RK stages
                                replayed from one hipGraph (captured on first use, valid
                                across tree changes; FP32)                              */

@@ -279,22 +279,53 @@ int do_update(mrfv_ctx *ctx, int stage, const double *dt, T *U, T *U0, const T *
 }
 
 // Whether the stages run fused, out of place through the state buffers W and W2 (every
-// context but the viscous ones, and those whose buffers could not be had).
+// context but the viscous ones, and those whose buffers were not to be had).
 bool fused_stages(const mrfv_ctx *ctx) { return ctx->d_W && ctx->d_W2 && !ctx->viscous; }
 
-// Contexts that did not get W and W2 when they were created (all but batched FP32) allocate
-// them with their first tree (steps allocate nothing, so that a caller may capture them);
-// where the memory is not there the stages go through L.
-int stage_buffers(mrfv_ctx *ctx) {
-    if (ctx->d_W || ctx->viscous || ctx->no_stage_buffers) return MRFV_OK;
+// Whether the caller is capturing the context's stream (or one that the null stream waits for).
+bool caller_captures(const mrfv_ctx *ctx) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &st) != hipSuccess) {
+        hipGetLastError();
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
+// W and W2 of the contexts that did not get them when they were created (all but batched
+// FP32): taken by the first global step outside a capture, never for local time stepping or
+// the operators, and only while at least half of the card's memory stays free: two padded
+// states are 1.1 MB per block in FP64 beside the 0.94 MB of everything else, and what a
+// caller allocates later has to fit as it does without them.  Else the stages go through L
+// (2304 leaves on five levels in FP64, a step: 4.04 ms through W and W2, 6.88 through L).
+void stage_buffers(mrfv_ctx *ctx) {
+    if (ctx->viscous || (ctx->cfg.batched && ctx->cfg.dtype == MRFV_F32)) return;
+    const bool capturing = caller_captures(ctx);
+    if (ctx->d_W) {
+        ctx->stage_buffers_captured = ctx->stage_buffers_captured || capturing;
+        return;
+    }
+    if (capturing || ctx->no_stage_buffers) return;
     const size_t bytes = (size_t)ctx->cfg.slot_capacity * 5 * CELLS_P * elem_size(ctx);
-    if (hipMalloc(&ctx->d_W, bytes) != hipSuccess || hipMalloc(&ctx->d_W2, bytes) != hipSuccess) {
+    size_t avail = 0, total = 0;
+    const bool room = hipMemGetInfo(&avail, &total) == hipSuccess && avail >= 2 * bytes + total / 2;
+    if (!room || hipMalloc(&ctx->d_W, bytes) != hipSuccess || hipMalloc(&ctx->d_W2, bytes) != hipSuccess) {
         if (ctx->d_W) hipFree(ctx->d_W);
         ctx->d_W = ctx->d_W2 = nullptr;
         ctx->no_stage_buffers = true;
+        ctx->err = "note: no memory to spare for the stage buffers, steps take separate right-hand side and update launches";
         hipGetLastError();   // the refusal is handled here
     }
-    return MRFV_OK;
+}
+
+// Gives W and W2 back for buffers that are needed; false if there was nothing to give (a graph
+// that the caller captured may hold their addresses: then they stay).
+bool release_stage_buffers(mrfv_ctx *ctx) {
+    if (!ctx->d_W || ctx->stage_buffers_captured || (ctx->cfg.batched && ctx->cfg.dtype == MRFV_F32)) return false;
+    hipFree(ctx->d_W);   // (waits for the device)
+    hipFree(ctx->d_W2);
+    ctx->d_W = ctx->d_W2 = nullptr;
+    return true;
 }
 
 // One fused stage: rhs + update over all leaves, then the jump correction on the updated
@@ -566,7 +597,7 @@ int do_init(mrfv_ctx *ctx, mrfv_ic_fn ic, void *user, T *U) {
     }
     CALL(do_project<T>(ctx, U));
     HIP_OK(hipStreamSynchronize(ctx->stream));
-    CALL(stage_buffers(ctx));
+    ctx->no_stage_buffers = false;   // a new tree asks again
     ctx->initialised = true;
     return MRFV_OK;
 }
@@ -588,6 +619,7 @@ int do_stages(mrfv_ctx *ctx, T *U, T *U0, T *Lb, double *dt) {
     } else {
         CALL(do_cfl<T>(ctx, U, dt));
     }
+    stage_buffers(ctx);
     if (fused_stages(ctx)) {
         // fused stages, out of place through two more state buffers: U -> W -> W2 -> U;
         // parents are restricted and filled only if some leaf face reads them.  Stages
@@ -963,7 +995,13 @@ int lts_buffers(mrfv_ctx *ctx) {
         {&ctx->d_ACC, cap * 6 * 5 * FACE * es}};
     for (auto &w : want) {
         if (*w.p) continue;
-        if (hipMalloc(w.p, w.bytes) != hipSuccess) {
+        hipError_t e = hipMalloc(w.p, w.bytes);
+        if (e != hipSuccess) {
+            hipGetLastError();   // handled here, or reported as MRFV_ENOMEM
+            if (release_stage_buffers(ctx)) e = hipMalloc(w.p, w.bytes);
+        }
+        if (e != hipSuccess) {
+            hipGetLastError();
             *w.p = nullptr;
             return fail(ctx, MRFV_ENOMEM, "hipMalloc of the local time stepping buffers failed");
         }

@@ -387,8 +387,9 @@ struct mrfv_ctx {
     double *d_static_totals = nullptr; // that device's static totals scratch (not owned)
     int32_t *d_err = nullptr;          // device error word
     void *d_W = nullptr, *d_W2 = nullptr;   // second and third padded state buffers
-                                            // (fused FP32 stages: U -> W -> W2 -> U)
+                                            // (fused stages: U -> W -> W2 -> U)
     bool no_stage_buffers = false;     // W and W2 could not be had: stages go through L
+    bool stage_buffers_captured = false;   // a caller's graph may hold their addresses
     void *d_FF = nullptr;              // boundary face fluxes [cap][6][5][16][16]
     void *d_Fp = nullptr, *d_H0 = nullptr, *d_ACC = nullptr;   // local time stepping, on first use
     double *d_blockred = nullptr;      // [cap][5] per-block partial reductions
