@@ -221,7 +221,6 @@ class Solver:
         self.flags = torch.zeros(cap, dtype=torch.int8, device=self.device)
         self.det = torch.zeros(cap, dtype=torch.float64, device=self.device)
         self.tot = torch.zeros((n, 5), dtype=torch.float64, device=self.device)
-        self._cb = None
         self.time = np.zeros(n)
 
     # -------------------------------------------------------------------- plumbing
@@ -257,8 +256,9 @@ class Solver:
             out = np.ctypeslib.as_array(prim, shape=(5 * NI ** 3,))
             out[:] = np.asarray(gen(inst, level, bx, by, bz), dtype=np.float64).reshape(-1)
 
-        self._cb = IC_FN(cb)
-        self._chk(lib().mrfv_init_blocks(self.h, self._cb, None, self._p(self.U)))
+        # the library calls it during this call only; kept on self it would make a cycle (it
+        # closes over self), and a dropped solver would hold its memory until a collection
+        self._chk(lib().mrfv_init_blocks(self.h, IC_FN(cb), None, self._p(self.U)))
         return self
 
     def fill_halos(self):
