@@ -671,25 +671,27 @@ int do_stages(mrfv_ctx *ctx, T *U, T *U0, T *Lb, double *dt) {
 // read their work lists through the gated device descriptors, so one capture serves every
 // later tree.  Captured on the library's own stream, launched on the caller's.
 // Which launches a captured step graph contains: the finest level present, whether
-// resolution jumps exist, which per-level lists are non-empty, and the fused kernel's split
-// of the leaves over workgroups.  Counts and list
-// contents are read on the device, so one graph serves every tree with the same key.
+// resolution jumps exist, which per-level lists are non-empty, the fused kernel's split of the
+// leaves over workgroups, and the size classes of the stage fills' lists (a level has three
+// bits: 0 empty, fill_class).  Counts and list contents are read on the device, so one graph
+// serves every tree with the same key.
 GraphKey graph_key(const mrfv_ctx *ctx) {
     const HostLists &L = ctx->lists;
     uint64_t k = (uint64_t)L.max_level | ((uint64_t)ctx->has_jumps << 4) |
                  ((uint64_t)L.parents_needed << 63) | ((uint64_t)ctx->cfl_from_stage << 62) |
                  ((uint64_t)ctx->restrict_from_stage << 61) | ((uint64_t)L.pars_copy_only << 60);
     uint64_t k2 = (uint64_t)rhs_slabs(L.all_leaves_cnt) << (3 * MAX_LEVELS);   // <= 8
+    uint64_t k3 = 0;
     for (int l = 0; l <= L.max_level && l < MAX_LEVELS; ++l) {
         if (L.desc[2 * desc_par(l) + 1] > 0) k |= 1ull << (5 + l);
-        if (L.desc[2 * desc_fitem(l) + 1] > 0) k |= 1ull << (5 + MAX_LEVELS + l);
+        k3 |= (uint64_t)fill_class(L.desc[2 * desc_fitem(l) + 1]) << (3 * l);
         if (L.desc[2 * desc_pproj(l) + 1] > 0) k |= 1ull << (5 + 3 * MAX_LEVELS + l);
         if (L.desc[2 * desc_jleaf26(l) + 1] > 0) k2 |= 1ull << l;   // the adaptation's fill
         if (L.desc[2 * desc_ffr(l) + 1] > 0) k2 |= 1ull << (44 + l);
         if (L.par_srestr[l]) k2 |= 1ull << (MAX_LEVELS + l);            // restriction passes
         if (L.pproj_srestr[l]) k2 |= 1ull << (2 * MAX_LEVELS + l);      // left out
     }
-    return {k, k2};
+    return {k, k2, k3};
 }
 
 void drop_graphs(mrfv_ctx *ctx) {

@@ -1008,29 +1008,38 @@ hipError_t launch_prim2cons(const double *prim, const int32_t *slots, int n, T *
     return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_fill_halos(T *U, const WorkList &wl, const DevTables &tb, FillMode mode,
-                             hipStream_t st) {
-    if (wl.grid <= 0) return hipSuccess;
-    // one workgroup per region (a stage's fill: per item, so that none starts for a region
-    // that is read in place and one launch covers a level's parents and leaves), except in
-    // the mode before the details (all 26 regions of
-    // the jump leaves, most of them read in place and skipped): two per block, 13 regions
-    // each (0.42 -> 0.38 ms per step of config 5; one workgroup per block in the stages'
-    // missing-faces mode measured no faster)
-    const int nreg = (mode & FILL_ITEMS) ? 1 : (mode & FILL_FACES) ? 6 : 26;
+// One workgroup per region (a stage's fill: per item, so that none starts for a region that is
+// read in place and one launch covers a level's parents and leaves), except in the mode before
+// the details (all 26 regions of the jump leaves, most of them read in place and skipped): two
+// per block, 13 regions each (0.42 -> 0.38 ms per step of the six-level shock-blobs tree; one
+// workgroup per block in the stages' missing-faces mode measured no faster).
+FillGrid fill_grid(int n, int grid, int mode, bool captured) {
+    const bool items = (mode & FILL_ITEMS) != 0;
+    if (captured && items) n = fill_class_end(fill_class(n));
+    const int nreg = items ? 1 : (mode & FILL_FACES) ? 6 : 26;
     // (short lists: as many more as make two thousand workgroups with two components, a region's
     // chain of loads being what they wait for: two steps of the four-level Rayleigh-Taylor tree
     // 3160 -> 3085 us, four of the Tait tube's 2295 -> 2215; twice as many workgroups made
     // Kelvin-Helmholtz's longer lists 1 % slower, half as many gave half of it)
-    const int gy = ((mode & FILL_MISSING) && !(mode & FILL_FACES)) ? std::clamp(1024 / std::max(1, wl.n), 2, 26) : nreg;
+    const int y = ((mode & FILL_MISSING) && !(mode & FILL_FACES)) ? std::clamp(1024 / std::max(1, n), 2, 26) : nreg;
     // few regions: a workgroup per component, since one takes its time from a chain of loads and
     // barriers per component (many regions: one for all, which shares the index arithmetic)
-    const int nz = (int64_t)wl.n * gy * 5 <= 4096 ? ((mode & FILL_RHO_E) ? 2 : 5) : 1;
-    // (a captured launch's grid is a bound: for a short list, one that loops rather than thousands
-    // of workgroups without a region)
-    const int gx = wl.desc && nz > 1 ? std::min(wl.grid, std::max(64, 2 * wl.n)) : wl.grid;
-    const dim3 grid(round_xcd(gx), gy, nz);
+    const int z = (int64_t)n * y * 5 <= FILL_SPLIT ? ((mode & FILL_RHO_E) ? 2 : 5) : 1;
+    // A captured launch's grid is a bound.  A short list of items gets its size class's, which
+    // the graph's key holds (3240 leaves whose finest list had grown from 24 items to 5184 since
+    // the capture, a step: 4.07 ms with a grid of the count at capture, 3.39 so; one for the
+    // longest short list cost 2 % of a step in surplus workgroups).  A short list of blocks gets one that loops: with 64 blocks, and
+    // more workgroups per block the fewer there are, at least 2048 workgroups whatever it grows to.
+    const int x = captured && z > 1 ? std::min(grid, items ? n : std::max(64, 2 * n)) : grid;
+    return {round_xcd(x), y, z};
+}
+
+template <typename T>
+hipError_t launch_fill_halos(T *U, const WorkList &wl, const DevTables &tb, FillMode mode,
+                             hipStream_t st) {
+    if (wl.grid <= 0) return hipSuccess;
+    const FillGrid f = fill_grid(wl.n, wl.grid, (int)mode, wl.desc != nullptr);
+    const dim3 grid(f.x, f.y, f.z);
     // (FP64 rows by element: two accesses per quad, 1 % slower on 360 leaves)
     const int vec = sizeof(T) == 4 && ((uintptr_t)U & 15) == 0;
     if (tb.ext_bc)

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <array>
 #include <cstdint>
 #include <string>
 #include <unordered_map>
@@ -232,6 +233,19 @@ constexpr int N_DESC = 5 + DESC_PER_LEVEL * MAX_LEVELS;
 enum FillMode { FILL_ALL = 0, FILL_FACES = 1, FILL_MISSING = 2, FILL_MISSING_FACES = 3, FILL_RHO_E = 4,
                 FILL_PRESENT = 8, FILL_ITEMS = 16, FILL_VISC = 32 };
 
+// Grid of a halo fill over n blocks or items (grid: the list's own bound; captured: into a step
+// graph, which serves other lists later).
+struct FillGrid {
+    int x, y, z;
+};
+FillGrid fill_grid(int n, int grid, int mode, bool captured);
+// Up to this many workgroups with a component each, a region's components are split.
+constexpr int FILL_SPLIT = 4096;
+// Size class of a list of fill items (0: empty, 4: not short): the captured launches of two
+// lists of one class are the same.
+constexpr int fill_class(int n) { return n <= 0 ? 0 : n <= 64 ? 1 : n <= 256 ? 2 : n <= FILL_SPLIT / 5 ? 3 : 4; }
+constexpr int fill_class_end(int c) { return c == 0 ? 0 : c == 1 ? 64 : c == 2 ? 256 : c == 3 ? FILL_SPLIT / 5 : 1 << 26; }
+
 // --------------------------------------------------------------- kernel launchers ----
 // All launchers enqueue on `st` and return hipGetLastError().
 template <typename T>
@@ -370,8 +384,9 @@ namespace mrfv {
 // The proposer network's forward pass queued on a given stream; logits [N][3] FP32.
 int mlp_forward_on(mrfv_mlp *mm, hipStream_t st, const float *X, int N, float *logits);
 }  // namespace mrfv
-// Which launches a captured step graph holds: two words of per-level list emptiness.
-using GraphKey = std::pair<uint64_t, uint64_t>;
+// Which launches a captured step graph holds: two words of per-level list emptiness, one of the
+// fill lists' size classes.
+using GraphKey = std::array<uint64_t, 3>;
 
 struct mrfv_ctx {
     mrfv_config cfg{};
