@@ -31,27 +31,23 @@ constexpr int TPB = 256;
 
 __device__ __forceinline__ float rcp_(float x) { return __builtin_amdgcn_rcpf(x); }
 // FP64: the hardware's estimate (2^-24.4 at worst) and two Newton steps, 5 instructions against
-// the 11 of an IEEE division.  For the normal numbers these kernels meet (densities, sums of
-// square roots, products of smoothness indicators >= 1e-24) rcp_, sqrt_ and their composition
-// rsqrt_ round as 1 / x, sqrt(x) and 1 / sqrt(x) do: the same in 5e8 draws from 1e-24 to 1e6.
-// A Newton rsqrt of its own, one unit off at times, moved gas at rest by 1e-17 and with it the
-// side some faces take their flux from: 1e-8 in the solution after a few steps.
+// the 11 of an IEEE division.  For finite x of magnitude 2^-1021 to 2^1021 it rounds as 1 / x
+// does (no difference in 5e8 draws from each of nine ranges of exponents in it).  The steps make
+// NaN of the infinity and the zero that 1 / 0 and 1 / inf are, so the callers pass neither, but
+// where their result is NaN anyway: densities, sums of square roots and wave speeds, indicators
+// and their products, bounded below by their eps.  Weights that vanish where a denominator
+// overflows take rcp_any_.
+// (A Newton rsqrt of its own, one unit off at times, moved gas at rest by 1e-17 and with it the
+// side some faces take their flux from: 1e-8 in the solution after a few steps.)
 __device__ __forceinline__ double rcp_(double x) {
     double r = __builtin_amdgcn_rcp(x);
     r = fma(r, fma(-x, r, 1.0), r);
     return fma(r, fma(-x, r, 1.0), r);
 }
 __device__ __forceinline__ float sqrt_(float x) { return __builtin_amdgcn_sqrtf(x); }
-__device__ __forceinline__ double sqrt_(double x) {   // x >= 0, Newton on the estimate of 1/sqrt(x)
-    const double y = __builtin_amdgcn_rsq(x);
-    double g = x * y, h = 0.5 * y;
-    double e = fma(-h, g, 0.5);
-    g = fma(g, e, g);
-    h = fma(h, e, h);
-    g = fma(fma(-g, g, x), h, g);
-    g = fma(fma(-g, g, x), h, g);
-    return x == 0.0 ? x : g;
-}
+// (IEEE: a Newton iteration of its own on the estimate of 1 / sqrt(x), for ordinary x only, took
+// 1 % off a step on 2304 leaves)
+__device__ __forceinline__ double sqrt_(double x) { return sqrt(x); }
 __device__ __forceinline__ float rsqrt_(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ __forceinline__ double rsqrt_(double x) { return rcp_(sqrt_(x)); }
 
@@ -200,9 +196,14 @@ __device__ __forceinline__ T wao53(T a, T b, T c, T d, T e) {
     const T b4 = fma(p1, p1, fma((T)(13.0 / 3.0) * p2, p2,
                                  fma((T)(781.0 / 20.0) * U3, U3, (T)(1421461.0 / 2275.0) * U4 * U4)));
     const T g1 = (T)(0.15 * 0.15 / 2.0), g2 = (T)(0.15 * 0.85), g3 = g1, g4 = (T)0.85;
+    // Candidates across jumps past 1e77 (in FP64; 1e9 in FP32), whose squared indicators overflow,
+    // have weight zero.  The FP64 rcp_ makes NaN of 1 / inf, and the maximum of a NaN and zero is
+    // zero (a NaN in the stencil stays one in the candidates).  HLLC on 480 leaves in FP64, a
+    // step: 1.35 ms without the maximum, 1.39 with it, 1.43 with a choice of results instead,
+    // 1.82 with a second, dividing evaluation for such lanes, which spills registers.
     auto wt = [&](T g, T beta) {
-        const T x = eps + beta;
-        return g * rcp_(x * x);
+        const T x = eps + beta, r = rcp_(x * x);
+        return g * (sizeof(T) == 8 ? fmax(r, (T)0) : r);
     };
     const T wl = wt(g1, b1), wc = wt(g2, b2), wr = wt(g3, b3), wh = wt(g4, b4);
     const T ql = fma((T)(5.0 / 6.0), u, (T)(-1.0 / 3.0) * w0);            // q_l - c
@@ -1351,7 +1352,7 @@ static void launch_alt(int variant, int stage, const double *dt, const float *Ui
 }
 
 // FP64: two planes per group and 512 threads, whose faces fill the LDS of a CU (138 KB) and
-// whose 219 registers leave two waves per SIMD.  Two workgroups of 256 threads with one plane
+// whose 221 registers leave two waves per SIMD.  Two workgroups of 256 threads with one plane
 // per group took 4 % longer on 2304 leaves and 16 % on 15 (a shear layer's step 6.12 against
 // 5.88 ms); three waves per SIMD spill 156 registers (10.6 ms).
 constexpr int F64_GP = 2, F64_TPB = 512;
