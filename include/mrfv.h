@@ -118,11 +118,13 @@ typedef struct {
                                instances in one fused rhs + update launch per stage, through
                                two more state buffers of mrfv_state_bytes each.  Contexts with
                                batched and MRFV_F32 allocate them in mrfv_create; the others
-                               in their first global step outside a stream capture, if half
-                               of the device's memory stays free then (mrfv_step_lts gives
-                               them back where it needs the memory).  Without them, and in
-                               viscous contexts, a stage is an rhs and an update launch
-                               through L; mrfv_last_error says so when they were refused.
+                               in their first global step outside a stream capture (in
+                               mrfv_init_blocks where both are within 1/256 of the device's
+                               memory), if half of the device's memory stays free then
+                               (mrfv_step_lts gives them back where it needs the memory).
+                               Without them, and in viscous contexts, a stage is an rhs
+                               and an update launch through L; mrfv_last_error says so
+                               where they were refused.
                                1: with MRFV_F32 also the entry points that need the two
                                buffers (mrfv_fused_stage, mrfv_autotune);
                                2: as 1, with the CFL step and the three RK stages

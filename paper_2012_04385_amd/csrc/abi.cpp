@@ -293,12 +293,15 @@ bool caller_captures(const mrfv_ctx *ctx) {
 }
 
 // W and W2 of the contexts that did not get them when they were created (all but batched
-// FP32): taken by the first global step outside a capture, never for local time stepping or
-// the operators, and only while at least half of the card's memory stays free: two padded
-// states are 1.1 MB per block in FP64 beside the 0.94 MB of everything else, and what a
-// caller allocates later has to fit as it does without them.  Else the stages go through L
+// FP32): taken by the first global step outside a capture, since local time stepping and the
+// operators use neither, and only while at least half of the card's memory stays free: two
+// padded states are 1.1 MB per block in FP64 beside the 0.94 MB of everything else, and what
+// a caller allocates later has to fit as it does without them.  Else the stages go through L
 // (2304 leaves on five levels in FP64, a step: 4.04 ms through W and W2, 6.88 through L).
-void stage_buffers(mrfv_ctx *ctx) {
+// with_tree: from mrfv_init_blocks, for contexts whose two buffers are within 1/256 of the card:
+// their first step is short beside the 60 us of the allocations (15 leaves in FP64, four
+// steps: 430 us against 490).
+void stage_buffers(mrfv_ctx *ctx, bool with_tree = false) {
     if (ctx->viscous || (ctx->cfg.batched && ctx->cfg.dtype == MRFV_F32)) return;
     const bool capturing = caller_captures(ctx);
     if (ctx->d_W) {
@@ -309,6 +312,7 @@ void stage_buffers(mrfv_ctx *ctx) {
     const size_t bytes = (size_t)ctx->cfg.slot_capacity * 5 * CELLS_P * elem_size(ctx);
     size_t avail = 0, total = 0;
     const bool room = hipMemGetInfo(&avail, &total) == hipSuccess && avail >= 2 * bytes + total / 2;
+    if (with_tree && !(room && 2 * bytes <= total / 256)) return;
     if (!room || hipMalloc(&ctx->d_W, bytes) != hipSuccess || hipMalloc(&ctx->d_W2, bytes) != hipSuccess) {
         if (ctx->d_W) hipFree(ctx->d_W);
         ctx->d_W = ctx->d_W2 = nullptr;
@@ -598,6 +602,7 @@ int do_init(mrfv_ctx *ctx, mrfv_ic_fn ic, void *user, T *U) {
     CALL(do_project<T>(ctx, U));
     HIP_OK(hipStreamSynchronize(ctx->stream));
     ctx->no_stage_buffers = false;   // a new tree asks again
+    stage_buffers(ctx, true);
     ctx->initialised = true;
     return MRFV_OK;
 }

@@ -61,6 +61,21 @@ def test_only_a_global_step_takes_them(torch_mod):
     assert before - _free(torch_mod) > lts + 1.5 * state
 
 
+@pytest.mark.parametrize("room", [True, False])
+def test_small_contexts_take_them_with_the_tree(torch_mod, room):
+    from paper_2012_04385_amd.mrfv import Solver
+    fill = None if room else _filler(torch_mod, 0.4 * torch_mod.cuda.mem_get_info()[1])
+    pb = W.sod_single_level()
+    pb.n0, pb.dx0 = (10, 10, 9), 1.0 / 160
+    g = Solver([pb], dtype="f64", batched=0)
+    state = g.capacity * 5 * CELLS_P * 8
+    before = _free(torch_mod)
+    g.init()
+    taken = before - _free(torch_mod)
+    assert taken > 1.5 * state if room else taken < state // 4
+    del fill
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 @pytest.mark.parametrize("bc", [(0, 1, 0), (2, 1, 0)])
 def test_refused_stages_match_the_oracle(orc, torch_mod, dtype, bc):
