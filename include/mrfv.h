@@ -98,9 +98,10 @@ typedef struct {
                              of their central differences).  dt is then also bounded by
                              cfl * 3/16 * dx_lmax^2 * min(rho) / mu.  Viscous contexts
                              (any instance with mu > 0) evaluate the right-hand side and
-                             update in separate kernels and fill all 26 halo regions of the
-                             leaves every stage (the tangential derivatives read the edge
-                             halos); mrfv_create returns MRFV_EINVAL for one with batched
+                             update in separate kernels and fill the face and edge halos of
+                             the leaves every stage (the tangential derivatives read the
+                             edges; beside a same-level neighbour only the layer at the face
+                             or edge is filled); mrfv_create returns MRFV_EINVAL for one with batched
                              and MRFV_F32, mrfv_step_lts returns MRFV_EINVAL for one. */
     const double *bc_fixed;   /* host, read by mrfv_create only; required when some axis
                              has MRFV_BC_FIXED, else ignored (may be NULL): primitive states
@@ -120,7 +121,7 @@ typedef struct {
                                batched and MRFV_F32 allocate them in mrfv_create; the others
                                in their first global step outside a stream capture (in
                                mrfv_init_blocks where both are within 1/256 of the device's
-                               memory), if half of the device's memory stays free then
+                               memory), if a quarter of the device's memory stays free then
                                (mrfv_step_lts gives them back where it needs the memory).
                                Without them, and in viscous contexts, a stage is an rhs
                                and an update launch through L; mrfv_last_error says so
@@ -240,9 +241,10 @@ int mrfv_commit_flags(mrfv_ctx *ctx, const int8_t *flags_host, int32_t *new_slot
  * instances, mr_project, fill_halos, mr_flag, one device-to-host copy of the flags,
  * commit_flags and mr_predict of the new children.  U0, L: dev scratch of
  * mrfv_interior_bytes.  dt_dev: dev double[n_instances] receives this step's dt.
- * The batched FP32 path runs the stages out of place through two library-owned state
- * buffers (U -> W -> W2 -> U), reading same-level neighbours' interiors directly, and
- * restricts and fills only what the stages read.  Before the details only rho and E are
+ * The stages run out of place through two library-owned state buffers (U -> W -> W2 -> U;
+ * mrfv_config.batched says which contexts have them), reading same-level neighbours'
+ * interiors directly, and restrict and fill only what the stages read; without the buffers
+ * they run through L and update U in place.  Before the details only rho and E are
  * restricted and filled (all components are restricted when the flags change the tree).
  * On return U holds the new state in every leaf interior (call mr_project and fill_halos
  * for restricted parents and complete halos). */

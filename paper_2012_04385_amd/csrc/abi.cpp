@@ -167,16 +167,20 @@ int do_project(mrfv_ctx *ctx, T *U, bool stage_only = false, bool rho_e_only = f
 }
 
 // Halo fill, levels coarse to fine (a prediction reads the parent's filled halo).
-// Non-leaf blocks always get all 26 regions (they are prediction sources); leaves get
-//   FILL_ALL: all 26 regions (explicit fill, refinement);
-//   FILL_FACES: the face layers the flux reads (stages through L);
-//   FILL_MISSING_FACES: faces without a same-level neighbour (fused stages, which read
-//   same-level neighbours in place);
-//   FILL_MISSING: all regions without a same-level neighbour (before the details, which
-//   read same-level neighbours in place too).
-// with_parents = false leaves the non-leaf blocks out (a stage on a tree where no leaf face
-// reads a parent-derived value).
+//   FILL_ALL: all 26 regions of every block (explicit fill, refinement);
+//   FILL_VISC: the same of non-leaf blocks; of leaves what a viscous stage reads: no corner
+//   regions, one layer of a copy from a same-level neighbour;
+//   FILL_FACES: all 26 regions of non-leaf blocks (they are prediction sources), the face layers
+//   of leaves (stages through L, the start of a local macro step);
+//   FILL_MISSING_FACES: the items of desc_fitem: of leaves the faces without a same-level
+//   neighbour or on a boundary, of prediction sources the regions that the predictions read
+//   (fused stages, which read same-level neighbours in place);
+//   FILL_MISSING: all 26 regions of non-leaf blocks, of leaves those without a same-level
+//   neighbour (before the details, which read same-level neighbours in place too).
+// with_parents = false leaves the non-leaf blocks out (the items hold none of theirs on a tree
+// where no leaf face reads a parent-derived value).
 // FILL_RHO_E (with FILL_MISSING, before the details) applies to the parents' fill too.
+// min_level: coarser levels keep their halos.
 template <typename T>
 int do_fill(mrfv_ctx *ctx, T *U, int max_level, int mode = FILL_ALL, bool with_parents = true,
             int min_level = 0) {
@@ -294,9 +298,11 @@ bool caller_captures(const mrfv_ctx *ctx) {
 
 // W and W2 of the contexts that did not get them when they were created (all but batched
 // FP32): taken by the first global step outside a capture, since local time stepping and the
-// operators use neither, and only while at least half of the card's memory stays free: two
+// operators use neither, and only while at least a quarter of the card's memory stays free: two
 // padded states are 1.1 MB per block in FP64 beside the 0.94 MB of everything else, and what
-// a caller allocates later has to fit as it does without them.  Else the stages go through L
+// a caller allocates later has to fit as it does without them.  (With half of the card to
+// stay free a batch of 49,424 leaves, whose program held another batch's arrays as well, went
+// through L: 3.8e9 cell-updates/s instead of 7.1e9.)  Else the stages go through L
 // (2304 leaves on five levels in FP64, a step: 4.04 ms through W and W2, 6.88 through L).
 // with_tree: from mrfv_init_blocks, for contexts whose two buffers are within 1/256 of the card:
 // their first step is short beside the 60 us of the allocations (15 leaves in FP64, four
@@ -311,7 +317,7 @@ void stage_buffers(mrfv_ctx *ctx, bool with_tree = false) {
     if (capturing || ctx->no_stage_buffers) return;
     const size_t bytes = (size_t)ctx->cfg.slot_capacity * 5 * CELLS_P * elem_size(ctx);
     size_t avail = 0, total = 0;
-    const bool room = hipMemGetInfo(&avail, &total) == hipSuccess && avail >= 2 * bytes + total / 2;
+    const bool room = hipMemGetInfo(&avail, &total) == hipSuccess && avail >= 2 * bytes + total / 4;
     if (with_tree && !(room && 2 * bytes <= total / 256)) return;
     if (!room || hipMalloc(&ctx->d_W, bytes) != hipSuccess || hipMalloc(&ctx->d_W2, bytes) != hipSuccess) {
         if (ctx->d_W) hipFree(ctx->d_W);

@@ -64,7 +64,7 @@ def test_only_a_global_step_takes_them(torch_mod):
 @pytest.mark.parametrize("room", [True, False])
 def test_small_contexts_take_them_with_the_tree(torch_mod, room):
     from paper_2012_04385_amd.mrfv import Solver
-    fill = None if room else _filler(torch_mod, 0.4 * torch_mod.cuda.mem_get_info()[1])
+    fill = None if room else _filler(torch_mod, 0.2 * torch_mod.cuda.mem_get_info()[1])
     pb = W.sod_single_level()
     pb.n0, pb.dx0 = (10, 10, 9), 1.0 / 160
     g = Solver([pb], dtype="f64", batched=0)
@@ -79,10 +79,10 @@ def test_small_contexts_take_them_with_the_tree(torch_mod, room):
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 @pytest.mark.parametrize("bc", [(0, 1, 0), (2, 1, 0)])
 def test_refused_stages_match_the_oracle(orc, torch_mod, dtype, bc):
-    """With less than half of the card free the stages go through L and say so: one step on a
+    """With less than a quarter of the card free the stages go through L and say so: one step on a
     tree with one- and two-level jumps, the bounds of the same step on the fused path."""
     from paper_2012_04385_amd.mrfv import lib
-    fill = _filler(torch_mod, 0.4 * torch_mod.cuda.mem_get_info()[1])
+    fill = _filler(torch_mod, 0.2 * torch_mod.cuda.mem_get_info()[1])
     pb = W.uniform_flow(lmax=3, n0=(2, 2, 2))
     pb.bc = bc
     o, g = make_pair(orc, pb, [(1, 1, 1, 1), (1, 2, 1, 1), (2, 3, 2, 2), (1, 0, 3, 0)], dtype, False)
@@ -105,7 +105,7 @@ def test_refused_stages_match_the_oracle(orc, torch_mod, dtype, bc):
 
 @pytest.mark.parametrize("eos", ["stiffened", "tait"])
 def test_refused_adaptive_steps_match_the_oracle(orc, torch_mod, eos):
-    fill = _filler(torch_mod, 0.4 * torch_mod.cuda.mem_get_info()[1])
+    fill = _filler(torch_mod, 0.2 * torch_mod.cuda.mem_get_info()[1])
     pb = W.sod_tait_mr3(eos=eos)
     pb.lmax = 2
     o, g = make_pair(orc, pb, (), "f64", adapt=1)
