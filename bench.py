@@ -17,7 +17,7 @@ Also measured on the same workload:
   * roofline: the fused kernel's average duration from HIP events around each launch on
     the library's stream (eager run with the autotuned shape), against the FP32 vector
     peak, plus its algorithmic HBM bandwidth and the counter-measured traffic;
-  * the FP64 plain path on the same workload (speed-up), and config 2 (the 3-level blast)
+  * FP64 on the same workload (unbatched: the fused kernel without step graphs; speed-up), and config 2 (the 3-level blast)
     as extra keys.
 Prints one JSON line on stdout; progress goes to stderr.
 """
@@ -223,18 +223,15 @@ def capacity_for(pbs):
 
 
 def lts_leg(pbs, dtype, warmup, macro_steps):
-    """Local time stepping (mrfv_step_lts on a per-block context in `dtype`: FP32 takes the
-    flux divergence from the fused stage kernel in its default launch shape, FP64 from the
-    plain flux kernel) against global steps of the same context from the same start, and
-    in FP32 against global steps of the batched path in the same shape (mrfv_run): simulated time
+    """Local time stepping (mrfv_step_lts on an unbatched context in `dtype`, the flux
+    divergence from the fused stage kernel, in FP32 in its default launch shape) against
+    global steps of the same context from the same start, and in FP32 against global steps of the batched path in the same shape (mrfv_run): simulated time
     advanced per second of wall clock (time to solution), and cell-updates per second per
     RK stage (leaf cells times their own steps)."""
     import torch
     from paper_2012_04385_amd.mrfv import Solver
     lmax = pbs[0].lmax
-    path = ("fused stage kernel (flux divergence) + local time stepping kernels" if dtype == "f32"
-            else "plain per-block kernels")
-    out = {"dtype": dtype, "path": path, "macro_steps": macro_steps,
+    out = {"dtype": dtype, "path": "fused stage kernel (flux divergence) + local time stepping kernels", "macro_steps": macro_steps,
            "micro_steps_per_macro_step": 1 << lmax}
     g = Solver(pbs, dtype=dtype, batched=0, capacity=capacity_for(pbs)).init()
     if dtype == "f32":
@@ -271,11 +268,11 @@ def lts_leg(pbs, dtype, warmup, macro_steps):
     free(g)
     out.update({"global_steps": steps, "global_ms_per_step": 1e3 * secs_g / steps,
                 "global_sim_time_per_s": sim_g / secs_g,
-                "time_to_solution_speedup": (sim / secs) / (sim_g / secs_g)})
+                "speedup_vs_unbatched_global": (sim / secs) / (sim_g / secs_g)})
     if dtype == "f32":
         # global steps on the fused batched path in the launch shape the local time
         # stepping context used, as a user runs them (mrfv_run: step graphs, the next step
-        # queued ahead): as many steps as the plain global leg took, whose CFL steps these
+        # queued ahead): as many steps as the unbatched global leg took, whose CFL steps these
         # repeat up to FP32 rounding, so they cover the same simulated time
         g = Solver(pbs, dtype=dtype, batched=2, capacity=capacity_for(pbs)).init()
         g.run(warmup * (1 << lmax))
@@ -338,7 +335,7 @@ def eos_leg(warmup, steps):
     and with the stiffened gas, unbatched contexts, FP32 and FP64: cell-updates per second and
     their ratio (Tait evolves four of the five components)."""
     from paper_2012_04385_amd import workloads as W
-    out = {"workload": "sod tube, 256 cells effective along x, l_max 3", "path": "plain per-block kernels",
+    out = {"workload": "sod tube, 256 cells effective along x, l_max 3", "path": "fused kernel, unbatched",
            "steps": steps, "warmup": warmup}
     for dtype in ("f32", "f64"):
         for eos in ("stiffened", "tait"):
@@ -381,7 +378,7 @@ def rti_leg(ks, t_end, dtype="f64"):
     from paper_2012_04385_amd.mrfv import Solver
     rh, rl, mu = W.RTI_FLUIDS[0.5]
     out = {"workload": "Rayleigh-Taylor, At 0.5, rho 1.5 | 0.5, mu 0.1, g 1, l_max 3, 128 cells per "
-                       "wavelength, 1280 along y", "dtype": dtype, "path": "plain per-block kernels + viscous",
+                       "wavelength, 1280 along y", "dtype": dtype, "path": "fused kernel (right-hand side), viscous and update kernels",
            "fit": "least-squares slope of ln d(t) over 3/sqrt(k) <= t <= t_end/sqrt(k)", "runs": []}
     for k in ks:
         pb = W.rti(k=k, atwood=0.5, lmax=3)
@@ -420,7 +417,7 @@ def schemes_leg(warmup, steps, parity_steps=2):
     Scaling" in its one-core size (Woodward-Colella blast along y, l_max 3, 128 x 512 x 128,
     CFL 0.9): per kernel the FP32 batched path's rate (step graph, autotuned shape) after
     `parity_steps` steps run next to the oracle (identical trees, L1 differences), and the
-    FP64 plain path's rate; times relative to the standard configuration (Roe-WENO5)."""
+    FP64 rate (unbatched); times relative to the standard configuration (Roe-WENO5)."""
     from paper_2012_04385_amd import workloads as W
     out = {"workload": "Woodward-Colella blast along y, 128 x 512 x 128 effective, l_max 3, CFL 0.9",
            "steps": steps, "warmup": warmup, "kernels": {}}
@@ -454,10 +451,10 @@ def schemes_leg(warmup, steps, parity_steps=2):
         pbs = [W.wc_blast_mr4(scheme, steps=warmup + steps)]
         g, c64, s64, _ = run_gpu(pbs, "f64", 0, warmup, steps)
         free(g)
-        r["fp64_plain_cell_updates_per_s"] = c64 / s64
+        r["fp64_cell_updates_per_s"] = c64 / s64
         out["kernels"][scheme] = r
         log(f"[bench] {scheme}: {r.get('cell_updates_per_s', float('nan')):.3e} cell-updates/s FP32 batched "
-            f"(CFL {r.get('fp32_cfl')}), {r['fp64_plain_cell_updates_per_s']:.3e} FP64 plain, "
+            f"(CFL {r.get('fp32_cfl')}), {r['fp64_cell_updates_per_s']:.3e} FP64, "
             f"parity {r.get('parity_vs_oracle', {}).get('trees_identical')} "
             f"L1(rho) {r.get('parity_vs_oracle', {}).get('l1_rho', float('nan')):.1e}")
     ref = out["kernels"]["roe_weno5"]
@@ -465,7 +462,7 @@ def schemes_leg(warmup, steps, parity_steps=2):
         # time per cell-update relative to the standard configuration
         if "cell_updates_per_s" in r and "cell_updates_per_s" in ref:
             r["time_vs_standard_fp32"] = ref["cell_updates_per_s"] / r["cell_updates_per_s"]
-        r["time_vs_standard_fp64"] = ref["fp64_plain_cell_updates_per_s"] / r["fp64_plain_cell_updates_per_s"]
+        r["time_vs_standard_fp64"] = ref["fp64_cell_updates_per_s"] / r["fp64_cell_updates_per_s"]
     return out
 
 
@@ -485,7 +482,7 @@ def main():
     ap.add_argument("--parity-steps", type=int, default=2,
                     help="first steps also run by the oracle (parity and CPU baseline)")
     ap.add_argument("--no-cpu", action="store_true", help="skip the oracle (parity, CPU baseline)")
-    ap.add_argument("--no-fp64", action="store_true", help="skip the FP64 plain path")
+    ap.add_argument("--no-fp64", action="store_true", help="skip the FP64 run")
     ap.add_argument("--no-extra", action="store_true",
                     help="skip the extra keys (config 2, local time stepping, Tait's equation)")
     ap.add_argument("--copy-calibration", action="store_true",
@@ -515,7 +512,7 @@ def main():
         for dtype in ("f32", "f64"):
             r = lts_leg(problems(args.workload, 10 ** 6), dtype, 1, args.lts_macro_steps)
             log(f"[bench] LTS {dtype}: {r['ms_per_macro_step']:.1f} ms per macro step, "
-                f"time-to-solution speed-up {r['time_to_solution_speedup']:.2f}")
+                f"time-to-solution speed-up {r['speedup_vs_unbatched_global']:.2f}")
             print(json.dumps(dict(r, workload=args.workload)), flush=True)
         return
     if args.schemes:
@@ -579,12 +576,12 @@ def main():
         g64, cells64, secs64, _ = run_gpu(pbs, "f64", 0, args.warmup, args.steps)
         free(g64)
         v64 = cells64 / secs64
-        log(f"[bench] FP64 plain: {v64:.4e} cell-updates/s")
-        extra.update({"fp64_plain_value": v64, "speedup_vs_fp64_plain": value / v64})
+        log(f"[bench] FP64: {v64:.4e} cell-updates/s")
+        extra.update({"fp64_value": v64, "speedup_vs_fp64": value / v64})
         # the baseline's own roofline: the same FLOP model per cell-update over the whole
         # step's rate (an upper bound on the flux kernel rate) against FP64 peak
         fpc64 = flops_per_cell_update(res.get("llf", 0.5))
-        extra["fp64_plain_roofline"] = {"bound": "alu", "achieved": v64 * fpc64 / 1e12,
+        extra["fp64_roofline"] = {"bound": "alu", "achieved": v64 * fpc64 / 1e12,
                                         "peak": PEAK_FP64_VECTOR / 1e12, "unit": "TFLOP/s",
                                         "frac": v64 * fpc64 / PEAK_FP64_VECTOR,
                                         "basis": "whole-step rate x FLOP model"}
@@ -597,8 +594,8 @@ def main():
         if not args.no_fp64:
             gb, cb64, sb64, _ = run_gpu(pb2, "f64", 0, 5, 45)
             free(gb)
-            c2["fp64_plain_value"] = cb64 / sb64
-            c2["speedup_vs_fp64_plain"] = c2["value"] / c2["fp64_plain_value"]
+            c2["fp64_value"] = cb64 / sb64
+            c2["speedup_vs_fp64"] = c2["value"] / c2["fp64_value"]
         extra["blast_128e_3lvl"] = c2
         log(f"[bench] config 2 (blast_128e_3lvl): {c2['value']:.4e} cell-updates/s")
 
@@ -606,7 +603,7 @@ def main():
         try:
             lt = lts_leg(pbs, "f32", 1, 2)
             extra["local_time_stepping"] = lt
-            log(f"[bench] LTS f32: time-to-solution speed-up {lt['time_to_solution_speedup']:.2f}")
+            log(f"[bench] LTS f32: time-to-solution speed-up {lt['speedup_vs_unbatched_global']:.2f}")
         except Exception as e:   # reported, not fatal: the headline stands on its own
             extra["local_time_stepping"] = {"error": str(e)}
         extra["tait_vs_stiffened"] = eos_leg(5, 30)

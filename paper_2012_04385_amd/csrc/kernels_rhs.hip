@@ -31,12 +31,13 @@ constexpr int TPB = 256;
 
 __device__ __forceinline__ float rcp_(float x) { return __builtin_amdgcn_rcpf(x); }
 // FP64: the hardware's estimate (2^-24.4 at worst) and two Newton steps, 5 instructions against
-// the 11 of an IEEE division.  For finite x of magnitude 2^-1021 to 2^1021 it rounds as 1 / x
-// does (no difference in 5e8 draws from each of nine ranges of exponents in it).  The steps make
-// NaN of the infinity and the zero that 1 / 0 and 1 / inf are, so the callers pass neither, but
-// where their result is NaN anyway: densities, sums of square roots and wave speeds, indicators
-// and their products, bounded below by their eps.  Weights that vanish where a denominator
-// overflows take rcp_any_.
+// the 11 of an IEEE division (a step on 2304 leaves 4.09 against 4.19 ms).  For finite x that is
+// not zero it rounds as 1 / x does (no difference in 5e8 draws from each of nine ranges of exponents
+// between 2^-1021 and 2^1023).  The steps make NaN of the infinity and the zero that 1 / 0 and
+// 1 / inf are.  The callers pass neither (densities, sums of square roots, wave speeds, indicators
+// and their products, which are bounded below by their eps), or have a NaN there anyway: WENO5's and
+// TENO5's products overflow at jumps past 3e38 and 1e154, where the sums they divide do too.  WENO-AO's
+// weights are the exception, see wao53.
 // (A Newton rsqrt of its own, one unit off at times, moved gas at rest by 1e-17 and with it the
 // side some faces take their flux from: 1e-8 in the solution after a few steps.)
 __device__ __forceinline__ double rcp_(double x) {
@@ -56,7 +57,7 @@ struct Gas {
     T g, B, gm1;
 };
 
-// Cell state along the pencil, momentum rotated to (normal, t1, t2).
+// Cell state of a stencil, momentum rotated to (normal, t1, t2).
 template <typename T>
 struct CellState {
     T r, mn, mt1, mt2, E, p, c, ir, sr;
@@ -691,12 +692,15 @@ constexpr int NFZ = NI * NI;                  // z-faces per face plane (256)
 // Slabs a leaf's planes are split into over workgroups (a power of two, at most 8 and at most
 // the kernel's groups).  A workgroup alone on its CU takes 93 us for a whole leaf, two at
 // once 146 us together (the chip holds two per CU), so a launch lasts about as long as its
-// fullest CU: 73 units per pair member, 93 for an odd one out, times the slab's share of the
-// leaf's faces.  Each slab repeats one plane of 256 z-faces beside 1600 per group of two
+// fullest of 256 CUs: 73 units per pair member, 93 for an odd one out, times the slab's share of
+// the leaf's faces.  Each slab repeats one plane of 256 z-faces beside 1600 per group of two
 // planes and starts and drains its own pipeline (taken as 500 faces).  The split with the
 // least of that is taken, the smaller on ties: 8 leaves go to 64 workgroups, 592
 // leaves (three on the fullest CU) to 1184, 512 leaves (two on every CU) and large trees
-// stay whole.  FP64 workgroups fill their CU alone (pairs = false).  Split launches have at most SLAB_ITEMS workgroups, which bounds the grid of a
+// stay whole.  FP64 workgroups fill their CU alone (pairs = false; the 93 is then a common factor).
+// A launch that writes CFL maxima splits into at most CFL_SLABS, the places it has per leaf: the
+// last stage of a step graph on 8 leaves goes to 32 workgroups and takes 29 us, the others 17.
+// Split launches have at most SLAB_ITEMS workgroups, which bounds the grid of a
 // captured one (a step graph's key holds the split of the tree it is launched for).
 constexpr int SLAB_ITEMS = 4096;
 int slab_split(int nleaf, int most, bool pairs) {
